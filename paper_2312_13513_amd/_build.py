@@ -23,12 +23,20 @@ HIPCC_FLAGS = ["-O3", "-fPIC", "-std=c++17", f"--offload-arch={ARCH}",
 # Machine-level loop-invariant code motion hoists every FP64 constant of the
 # mechanism (and every per-element slot address) out of the cell loop into
 # registers, which then spill to scratch (about 1 KB per lane); without it
-# the kernels need no scratch at all.
+# the kernels need no scratch at all.  The lane-group integrators hold a row
+# of the Newton matrix per lane and lose those registers the same way.
 NO_MACHINE_LICM = ["-mllvm", "-disable-machine-licm"]
+
+
+# Merging the tails of the per-order code of the lane-group integrators turns
+# the Nordsieck columns into an array with a variable index, in memory.
+NO_SINK = ["-mllvm", "-simplifycfg-sink-common=false"]
 
 
 def per_file_flags(src: str) -> list:
     name = os.path.basename(src)
+    if name.startswith("bdf_wave"):
+        return NO_MACHINE_LICM + NO_SINK
     if name.startswith("gen_") or name == "chem_kernels.hip":
         return NO_MACHINE_LICM
     return []

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "chem_internal.h"
+#include "wave_tables.h"
 
 namespace chem {
 
@@ -26,7 +27,7 @@ bool wave_uses_global_scratch(const DevMechView &m, int lanes);
 // (N <= 16).  qscratch holds max_groups slices of 7 R doubles, used when the
 // reaction scratch does not fit in LDS
 // (wave_uses_global_scratch); the launch then runs at most max_groups groups.
-hipError_t launch_bdf_wave(const DevMechView &m, const WaveTables &wt, double *T, const double *p,
+hipError_t launch_bdf_wave(const DevMechView &m, const WaveTables &wt, const Wave64Tables &w64, double *T, const double *p,
                            double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
                            int32_t *status, int32_t *counters, unsigned long long *queue,
                            double *qscratch, int max_groups, bool fp32_lu, int lanes, hipStream_t s);

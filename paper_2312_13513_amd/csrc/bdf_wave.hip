@@ -3,21 +3,25 @@
 //
 // A group of G lanes owns one cell at a time and takes the next from a work
 // queue as soon as that cell is done.  Lane i owns component i of every state
-// vector (Nordsieck column, correction, weights); the Newton matrix and its
-// LU factors live in LDS (lane i: row i); lanes cooperate on the right-hand
-// side (lane k: thermo of species k; lane j: reactions j, j+G, ...) through
-// LDS.  Sums over reactions are gathered by the owning species lane in a
-// fixed order, so results do not depend on timing.  Control flow is uniform
+// vector (Nordsieck column, correction, weights).  Control flow is uniform
 // within a group: every decision of the integrator contract (the same as the
 // one-thread-per-cell driver and the CPU oracle) is taken once per cell, so
 // cells of very different stiffness do not hold each other back; the groups
-// of one wave diverge like the lanes of any SIMT program.
+// of one wave diverge like the lanes of any SIMT program.  Sums over
+// reactions run in a fixed order, so results do not depend on timing.
+//
+// Two systems provide the right-hand side, the Newton matrix and the solve:
+//  * GroupSys (this file): the Newton matrix and its LU factors in LDS (lane
+//    i: row i); for the tile and, with the same operations, for the wave of a
+//    mechanism that fits the tile (N <= 16);
+//  * WaveSys (wave_system.h): the inverse of the Newton matrix in registers
+//    and every sum dealt out over 64 lanes; for larger mechanisms.
 //
 // NP is the padded row count (a compile-time bound on N = K+1 <= 64).  LT is
-// the type of the Jacobian, the Newton matrix, its LU factors and the
-// triangular solves: double (plain FP64) or float (mixed precision: those in
-// FP32; residuals, state, norms, error control and the equilibrium constants
-// in FP64, so that the Newton iteration restores the accuracy).
+// the type of the Jacobian, the Newton matrix, its factors (or inverse) and
+// the solves: double (plain FP64) or float (mixed precision: those in FP32;
+// residuals, state, norms, error control and the equilibrium constants in
+// FP64, so that the Newton iteration restores the accuracy).
 
 #include "bdf_driver.h"
 #include "bdf_wave.h"
@@ -33,6 +37,7 @@
 namespace chem {
 namespace {
 
+constexpr int kDeferPasses = 3;   // passes a tile waits for another one's refresh at most
 constexpr bool kPD = CHEM_WAVE_PDEP != 0;
 
 // Lanes that own one cell: Grp<64> is a whole wave (one cell per wave),
@@ -527,45 +532,147 @@ __device__ __forceinline__ double wave_solve(const WaveLds<NP, LT, G> &L, int N,
     return lane < N ? (double)x : 0.0;
 }
 
-// One group of G lanes integrates one cell at a time and takes the next from
-// the work queue as soon as its cell is done, whatever the other groups of
-// the wave are doing: each pass of the loop is one step of the group's cell
-// (preceded by taking and starting a new cell when the group has none).
-template <int NP, typename LT, int G, bool DEFER>
-__device__ void run_cells(const DevMechView &m, const WaveTables &wt, const CellIO &io,
-                          double t_end, unsigned long long *queue, double *qbuf,
-                          WaveLds<NP, LT, G> &L)
-{
-    using namespace bdf;
-    using Gp = Grp<G>;
-    const int lane = Gp::lane();
-    const int K = m.K, N = K + 1;
-    const double rtol = io.prm->rtol, atol = io.prm->atol;
+// The cell of a group of G lanes by the functions above: the tile (G = 16),
+// and the whole wave for small mechanisms.
+template <int NP, typename LT, int GL>
+struct GroupSys {
+    static constexpr int G = GL;
+    static constexpr bool kUniformOrder = false;   // the same code for the tile and the wave
+    using Gp = Grp<GL>;
+    const DevMechView &m;
+    const WaveTables &wt;
+    WaveLds<NP, LT, GL> &L;
+    double *qbuf;
+    int K;
     SpeciesLane sp;
+    int pi;       // factorisation's row permutation (this lane's entry)
+    LT dinv;      // reciprocal of this lane's diagonal element of U
+
+    __device__ GroupSys(const DevMechView &m_, const WaveTables &wt_, WaveLds<NP, LT, GL> &L_, double *qbuf_)
+        : m(m_), wt(wt_), L(L_), qbuf(qbuf_), K(m_.K)
     {
+        const int lane = Gp::lane();
         const int k = lane < K ? lane : 0;
         sp.blk = m.species + k * kSpeciesLen;
         sp.W = m.W[k];
         sp.invW = m.invW[k];
+        if (lane <= K) L.invW[lane] = lane < K ? sp.invW : 0.0;
+        pi = lane;
+        dinv = (LT)0;
+        Gp::sync();
     }
-    if (lane <= K) L.invW[lane] = lane < K ? sp.invW : 0.0;
-    Gp::sync();
+    __device__ __forceinline__ double rhs(double p, double yi)
+    {
+        return wave_rhs<NP, LT, GL>(m, wt, L, sp, K, p, yi, qbuf);
+    }
+    __device__ __forceinline__ bool refresh(double p, double yi, double gamma)
+    {
+        wave_newton_matrix<NP, LT, GL>(m, wt, L, sp, K, p, yi, gamma, qbuf);
+        return wave_lu<NP, LT, GL>(L, K + 1, pi, dinv);
+    }
+    __device__ __forceinline__ double solve(double bi) const
+    {
+        return wave_solve<NP, LT, GL>(L, K + 1, pi, dinv, bi);
+    }
+};
+
+#include "wave_system.h"
+
+// One group of lanes integrates one cell at a time and takes the next from
+// the work queue as soon as its cell is done, whatever the other groups of
+// the wave are doing.  Sys: the cell's right-hand side, Newton matrix and
+// solve on its group.  Each pass of the loop is one right-hand side of the
+// group's cell, with one call site for all its uses (start, Newton iteration,
+// restart): the integration's code stays small enough for the instruction
+// cache and its registers, and the groups of a wave share every evaluation
+// whatever phase they are in.  Measured on the 9-species tile against a pass
+// per step with a call site per use: 262,144 flame cells 7.44 -> 6.54 ms,
+// 257 random cells 2.91 -> 2.51 ms.
+// Uniform step data of a group, kept in LDS: the same for every lane, it would
+// take 60 registers of each.
+struct StepLds {
+    double tau[kQmax + 2];    // past step sizes, tau[1] most recent
+    // of the attempt: xi_i = (h + tau_1 + ... + tau_{i-1}) / h, the products
+    // xi_1 .. xi_i and the sums of 1 / xi_1 .. 1 / xi_i, and the coefficients l of
+    // prod_{i=1..q} (1 + x / xi_i)
+    double xi[kQmax + 2], pxi[kQmax + 2], sxi[kQmax + 2], l[kQmax + 1];
+    double fact[kQmax + 3];   // factorials
+};
+
+// f(q) with the order as a constant where it is uniform over the wave (CONST),
+// so that the loops over it are straight code, else as it is.
+template <bool CONST, class F>
+__device__ __forceinline__ void with_order(int q, F &&f)
+{
+    if constexpr (CONST) {
+        switch (q) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        default: f(std::integral_constant<int, 5>{}); break;
+        }
+    } else {
+        f(q);
+    }
+}
+
+template <class Sys, bool DEFER>
+__device__ void run_cells(Sys &S, StepLds &C, const CellIO &io, double t_end, unsigned long long *queue)
+{
+    using namespace bdf;
+    using Gp = Grp<Sys::G>;
+    enum : int { FIRST, STEP0, ITERATE, AGAIN };   // what the next right-hand side is for
+    const int lane = Gp::lane();
+    const int K = S.K, N = K + 1;
+    const double rtol = io.prm->rtol, atol = io.prm->atol;
     const bool active = lane < N;
-    int lu_pi = lane;       // factorisation's row permutation (this lane's entry)
-    LT lu_dinv = (LT)0;     // reciprocal of this lane's diagonal element of U
     // the group's cell and its integration state
     bool busy = false;
     int64_t cell = 0;
-    double p = 0.0, w = 0.0, h = 0.0, t = 0.0;
-    double z[kQmax + 1], tau[kQmax + 2];
+    double p = 0.0, w = 0.0, h = 0.0, t = 0.0, e = 0.0;
+    double z[kQmax + 1];
+    double xq1 = 0.0, inv_l1 = 0.0, gamma = 0.0, Cq = 0.0, dscale = 1.0;
+    double f0 = 0.0, hg = 0.0, hub = 0.0;                 // initial step
     int nst = 0, nfe = 0, nje = 0, nni = 0, netf = 0, ncfn = 0, status = 0;
-    int q = 1, qwait = 2, nst_M = 0;
-    bool have_M = false, ehat_ok = false;
-    bool waited = false;    // the group sat out the last pass (refresh deferral)
+    int phase = FIRST, q = 1, qwait = 2, nst_M = 0, it = 0, nef = 0, ncf = 0;
+    bool have_M = false, ehat_ok = false, need_M = false, jcur = false, force_M = false, last = false;
+    bool new_step = false, new_attempt = false;
+    int waited = 0;         // passes the group has sat out before this refresh
     unsigned long long ticket = 0;   // the group's last work-queue position
-    double gamma_M = 0.0, crate = 1.0, ehat_h = 0.0, ehat = 0.0;
-    auto wnorm = [&](double v) { const double u = active ? v * w : 0.0; return sqrt(Gp::sum(u * u) * (1.0 / N)); };
-    auto all_finite = [&](double v) { return Gp::ballot(active && !isfinite(v)) == 0ull; };
+    double gamma_M = 0.0, crate = 1.0, del_old = 0.0, dsm = 0.0, ehat_h = 0.0, ehat = 0.0;
+    auto wnorm = [&](double v) __attribute__((always_inline)) { const double u = active ? v * w : 0.0; return sqrt(Gp::sum(u * u) * (1.0 / N)); };
+    auto all_finite = [&](double v) __attribute__((always_inline)) { return Gp::ballot(active && !isfinite(v)) == 0ull; };
+    constexpr bool UQ = Sys::kUniformOrder;
+    auto rescale = [&](double eta) __attribute__((always_inline)) {
+        with_order<UQ>(q, [&](auto Q) __attribute__((always_inline)) {
+            double f = 1.0;
+            static_for<1, kQmax + 1>([&](auto j) __attribute__((always_inline)) {
+                f *= eta;
+                if (j <= Q) z[j] *= f;
+            });
+        });
+    };
+    auto unpredict = [&]() __attribute__((always_inline)) {
+        with_order<UQ>(q, [&](auto Q) __attribute__((always_inline)) {
+            static_for<0, kQmax>([&](auto m) __attribute__((always_inline)) {
+                constexpr int kk = kQmax - decltype(m)::value;
+                static_for<kk, kQmax + 1>([&](auto j) __attribute__((always_inline)) {
+                    if (j <= Q && kk <= Q) z[j - 1] -= z[j];
+                });
+            });
+        });
+    };
+    auto top_column = [&]() __attribute__((always_inline)) {
+        double zq = 0.0;
+        with_order<UQ>(q, [&](auto Q) __attribute__((always_inline)) {
+            static_for<2, kQmax + 1>([&](auto j) __attribute__((always_inline)) {
+                if (j == Q) zq = z[j];
+            });
+        });
+        return zq;
+    };
+    if (lane < kQmax + 3) C.fact[lane] = factorial_d(lane);
     for (;;) {
         if (!busy) {
             unsigned long long c = 0;
@@ -583,384 +690,352 @@ __device__ void run_cells(const DevMechView &m, const WaveTables &wt, const Cell
             else if (lane == K) y0 = io.T[cell];
             nst = nfe = nje = nni = netf = ncfn = 0;
             status = 0;
-            // ---------------- initial derivative and step ----------------
-            const double f0 = wave_rhs<NP, LT, G>(m, wt, L, sp, K, p, y0, qbuf);
-            nfe++;
-#pragma unroll
-            for (int j = 0; j <= kQmax; j++) z[j] = 0.0;
             z[0] = y0;
-            w = active ? 1.0 / (rtol * fabs(y0) + atol) : 0.0;
-            if (!all_finite(f0)) {
-                status = 4;
-            }
-            h = t_end;
-            if (status == 0 && wnorm(f0) != 0.0) {
-                double hub = t_end;
-                {
-                    // hub = min over components of (0.1|y0| + 1/w)/|f0| where it binds
-                    double lim = active ? 0.1 * fabs(y0) + 1.0 / w : 0.0;
-                    // sequential in component order, like the definition
-                    for (int i = 0; i < N; i++) {
-                        const double fi = Gp::at(f0, i), li = Gp::at(lim, i);
-                        if (fabs(fi) * hub > li) hub = li / fabs(fi);
-                    }
-                }
-                double hg = hub;
-                for (int it = 0; it < kH0Iters; it++) {
-                    const double f1 = wave_rhs<NP, LT, G>(m, wt, L, sp, K, p, y0 + hg * f0, qbuf);
-                    nfe++;
-                    if (!all_finite(f1)) {
-                        hg *= 0.1;
-                        continue;
-                    }
-                    const double ydd = wnorm((f1 - f0) / hg);
-                    double hnew = ydd > 0.0 ? sqrt(2.0 / ydd) : hub;
-                    if (hnew > hub) hnew = hub;
-                    const double ratio = hnew / hg;
-                    hg = hnew;
-                    if (ratio >= 0.5 && ratio <= 2.0) break;
-                }
-                h = 0.5 * hg;
-                if (h > t_end) h = t_end;
-            }
-            z[1] = h * f0;
-            q = 1;
-            qwait = 2;
-            nst_M = 0;
-            have_M = false;
-            ehat_ok = false;
-            gamma_M = 0.0;
-            crate = 1.0;
-            ehat_h = 0.0;
-            ehat = 0.0;
-            t = 0.0;
 #pragma unroll
-            for (int j = 0; j < kQmax + 2; j++) tau[j] = 0.0;
+            for (int j = 1; j <= kQmax; j++) z[j] = 0.0;
+            w = active ? 1.0 / (rtol * fabs(y0) + atol) : 0.0;
+            phase = FIRST;
+            new_step = new_attempt = need_M = false;
+            waited = 0;
         }
-        do {   // one step of the cell; break ends the step early
-            if (status != 0 || t >= t_end) break;
+        if (new_step) {
+            new_step = false;
             if (nst >= io.prm->max_steps) {
                 status = 1;
-                break;
+            } else {
+                last = false;
+                if (t + h >= t_end) {
+                    rescale((t_end - t) / h);
+                    h = t_end - t;
+                    last = true;
+                }
+                w = active ? rcp_d(rtol * fabs(z[0]) + atol) : 0.0;
+                nef = ncf = 0;
+                force_M = false;
+                new_attempt = true;
             }
-            if constexpr (Gp::kCells > 1 && DEFER) {
+        }
+        if (new_attempt && status == 0) {
+            new_attempt = false;
+            const double tnew = t + h;
+            if (tnew == t) status = 2;
+            double l1 = 1.0;
+            const double invh = rcp_d(h);
+            with_order<UQ>(q, [&](auto Q) __attribute__((always_inline)) {
+                static_for<1, kQmax + 1>([&](auto kk) __attribute__((always_inline)) {
+                    static_for<0, kQmax + 1 - decltype(kk)::value>([&](auto m) __attribute__((always_inline)) {
+                        constexpr int j = kQmax - decltype(m)::value;
+                        if (j <= Q) z[j - 1] += z[j];
+                    });
+                });
+                double s = h, px = 1.0, sx = 1.0, l[kQmax + 1];
+                l[0] = l[1] = 1.0;
+                static_for<2, kQmax + 1>([&](auto j) __attribute__((always_inline)) { l[j] = 0.0; });
+                C.xi[1] = C.pxi[1] = C.sxi[1] = 1.0;
+                static_for<2, kQmax + 2>([&](auto i) __attribute__((always_inline)) {
+                    if (i <= Q + 1) {
+                        s += C.tau[i - 1];
+                        const double rxi = h * rcp_d(s);
+                        xq1 = s * invh;
+                        px *= xq1;
+                        sx += rxi;
+                        C.xi[i] = xq1;
+                        C.pxi[i] = px;
+                        C.sxi[i] = sx;
+                        if constexpr (decltype(i)::value <= kQmax)
+                            if (i <= Q)
+                                static_for<0, decltype(i)::value>([&](auto m) __attribute__((always_inline)) {
+                                    constexpr int j = decltype(i)::value - decltype(m)::value;
+                                    l[j] += l[j - 1] * rxi;
+                                });
+                    }
+                });
+                l1 = l[1];
+                static_for<0, kQmax + 1>([&](auto j) __attribute__((always_inline)) { C.l[j] = l[j]; });
+            });
+            inv_l1 = rcp_d(l1);
+            gamma = h * inv_l1;
+            Cq = rcp_d(1.0 + l1 * xq1);
+            jcur = false;
+            const double gr = gamma * rcp_d(gamma_M);
+            need_M = !have_M || force_M || nst >= nst_M + kMsbp || fabs(gr - 1.0) > kDgmax;
+            // the correction of a solve with the factors of another gamma
+            dscale = gamma != gamma_M ? 2.0 * rcp_d(1.0 + gr) : 1.0;
+            it = 0;
+            e = 0.0;
+            del_old = 0.0;
+            phase = ITERATE;
+        }
+        bool ok_M = true;
+        // groups of the wave still in their initial step
+        int n_start = 0;
+        if constexpr (Gp::kCells > 1) n_start = __popcll(__ballot(lane == 0 && status == 0 && phase < ITERATE));
+        if (need_M && status == 0) {
+            if constexpr (Gp::kCells > 1) {
                 // The cells of a wave share its instruction stream: a Newton
                 // matrix refresh (Jacobian and LU) for one of them costs the
-                // whole wave.  A cell whose step will start with a refresh
-                // sits out one pass unless another cell of the wave needs one
-                // too (or it is the only cell stepping), so refreshes are
-                // shared more often.  Only while more cells were queued than
-                // the grid holds groups when this one took its cell: in the
-                // tail the slowest cell's latency is the run time, and waiting
-                // would lengthen it.  Its state is untouched while it waits:
-                // results do not depend on this.  The test estimates the
-                // step's gamma = h / l_1, l_1 = sum of 1/xi_i over the order;
-                // the refresh itself is decided exactly inside the step.
-                bool need = false;
-                if ((unsigned long long)io.nq - ticket > (unsigned long long)gridDim.x * Gp::kCells) {
-                    const double hh = (t + h >= t_end) ? t_end - t : h;
-                    double l1 = 0.0, s = hh;
-#pragma unroll
-                    for (int i = 1; i <= kQmax; i++)
-                        if (i <= q) {
-                            l1 += hh / s;
-                            s += tau[i];
-                        }
-                    need = !have_M || nst >= nst_M + kMsbp || fabs((hh / l1) / gamma_M - 1.0) > kDgmax;
-                }
-                const bool lead = lane == 0;
-                const int n_need = __popcll(__ballot(lead && need));
-                const int n_step = __popcll(__ballot(lead));
-                if (need && !waited && n_need < 2 && n_step >= 2) {
-                    waited = true;
-                    break;
-                }
-                waited = false;
-            }
-            bool last = false;
-            if (t + h >= t_end) {
-                const double eta = (t_end - t) / h;
-                double f = 1.0;
-#pragma unroll
-                for (int j = 1; j <= kQmax; j++) {
-                    f *= eta;
-                    if (j <= q) z[j] *= f;
-                }
-                h = t_end - t;
-                last = true;
-            }
-            w = active ? 1.0 / (rtol * fabs(z[0]) + atol) : 0.0;
-            int nef = 0, ncf = 0;
-            bool force_M = false;
-            double dsm = 0.0, e = 0.0;
-            double xi[kQmax + 2], l[kQmax + 1];
-            for (;;) {
-                const double tnew = t + h;
-                if (tnew == t) {
-                    status = 2;
-                    break;
-                }
-#pragma unroll
-                for (int kk = 1; kk <= kQmax; kk++)
-#pragma unroll
-                    for (int j = kQmax; j >= kk; j--)
-                        if (j <= q) z[j - 1] += z[j];
-                {
-                    double s = h;
-                    xi[1] = 1.0;
-#pragma unroll
-                    for (int i = 2; i <= kQmax + 1; i++) {
-                        s += tau[i - 1];
-                        xi[i] = s / h;
-                    }
-                    l[0] = 1.0;
-#pragma unroll
-                    for (int j = 1; j <= kQmax; j++) l[j] = 0.0;
-#pragma unroll
-                    for (int i = 1; i <= kQmax; i++)
-                        if (i <= q)
-#pragma unroll
-                            for (int j = i; j >= 1; j--) l[j] += l[j - 1] / xi[i];
-                }
-                const double gamma = h / l[1];
-                double xq1 = h;
-#pragma unroll
-                for (int i = 1; i <= kQmax; i++)
-                    if (i <= q) xq1 += tau[i];
-                xq1 /= h;
-                const double Cq = 1.0 / (1.0 + l[1] * xq1);
-                bool jcur = false, conv = false, lu_ok = true;
-                if (!have_M || force_M || nst >= nst_M + kMsbp || fabs(gamma / gamma_M - 1.0) > kDgmax) {
-                    wave_newton_matrix<NP, LT, G>(m, wt, L, sp, K, p, z[0], gamma, qbuf);
-                    nje++;
-                    lu_ok = wave_lu<NP, LT, G>(L, N, lu_pi, lu_dinv);
-                    gamma_M = gamma;
-                    nst_M = nst;
-                    crate = 1.0;
-                    have_M = lu_ok;
-                    jcur = true;
-                    force_M = false;
-                }
-                if (lu_ok) {
-                    double del_old = 0.0;
-                    e = 0.0;
-                    const double inv_l1 = 1.0 / l[1];
-                    for (int it = 0; it < kMaxCor; it++) {
-                        const double fy = wave_rhs<NP, LT, G>(m, wt, L, sp, K, p, z[0] + e, qbuf);
-                        nfe++;
-                        if (!all_finite(fy)) break;
-                        double d = active ? -(e - gamma * fy + z[1] * inv_l1) : 0.0;
-                        d = wave_solve<NP, LT, G>(L, N, lu_pi, lu_dinv, d);
-                        if (!active) d = 0.0;
-                        if (gamma != gamma_M) d *= 2.0 / (1.0 + gamma / gamma_M);
-                        const double dl = wnorm(d);
-                        e += d;
-                        nni++;
-                        if (it > 0) crate = fmax(kCrdown * crate, dl / del_old);
-                        const double dcon = dl * fmin(crate, 1.0) * Cq / kNlscoef;
-                        if (dcon <= 1.0) {
-                            conv = true;
-                            break;
-                        }
-                        if (it > 0 && dl > kRdiv * del_old) break;
-                        del_old = dl;
-                    }
-                }
-                if (!conv) {
-#pragma unroll
-                    for (int kk = kQmax; kk >= 1; kk--)
-#pragma unroll
-                        for (int j = kk; j <= kQmax; j++)
-                            if (j <= q && kk <= q) z[j - 1] -= z[j];
-                    if (!jcur) {
-                        force_M = true;
-                        continue;
-                    }
-                    ncfn++;
-                    if (++ncf >= kMaxNcf) {
-                        status = 3;
-                        break;
-                    }
-                    double f = 1.0;
-#pragma unroll
-                    for (int j = 1; j <= kQmax; j++) {
-                        f *= kEtaCf;
-                        if (j <= q) z[j] *= f;
-                    }
-                    h *= kEtaCf;
-                    last = false;
+                // whole wave.  So a cell's first refresh waits for the cells
+                // of the wave that are still in their initial step (up to
+                // five right-hand sides), which will need theirs too; and
+                // with DEFER any refresh waits up to kDeferPasses passes until
+                // another cell needs one too, only while more cells were
+                // queued than the grid holds groups when this one took its
+                // cell: in the tail the slowest cell's latency is the run
+                // time, and waiting would lengthen it.  A cell's state is
+                // untouched while it waits: results do not depend on this.
+                bool wait = !have_M && n_start > 0 && waited <= kH0Iters;
+                if constexpr (DEFER)
+                    wait = wait || ((unsigned long long)io.nq - ticket > (unsigned long long)gridDim.x * Gp::kCells &&
+                                    waited < kDeferPasses && __popcll(__ballot(lane == 0)) < 2);
+                if (wait) {
+                    waited++;
                     continue;
                 }
-                dsm = Cq * wnorm(e);
-                if (dsm > 1.0) {
+                waited = 0;
+            }
+            ok_M = S.refresh(p, z[0], gamma);
+            nje++;
+            gamma_M = gamma;
+            dscale = 1.0;
+            nst_M = nst;
+            crate = 1.0;
+            have_M = ok_M;
+            jcur = true;
+            force_M = false;
+            need_M = false;
+        }
+        bool conv = false, fail = !ok_M;
+        if (status == 0 && ok_M) {
+            // ---------------- right-hand side ----------------
+            const double f = S.rhs(p, phase == ITERATE ? z[0] + e : (phase == STEP0 ? z[0] + hg * f0 : z[0]));
+            nfe++;
+            const bool finite = all_finite(f);
+            if (phase == ITERATE) {
+                if (!finite) {
+                    fail = true;
+                } else {
+                    double d = active ? -(e - gamma * f + z[1] * inv_l1) : 0.0;
+                    d = S.solve(d);
+                    if (!active) d = 0.0;
+                    d *= dscale;
+                    const double dl = wnorm(d);
+                    e += d;
+                    nni++;
+                    if (it > 0) crate = fmax(kCrdown * crate, dl * rcp_d(del_old));
+                    conv = dl * fmin(crate, 1.0) * Cq <= kNlscoef;
+                    fail = !conv && ((it > 0 && dl > kRdiv * del_old) || it + 1 >= kMaxCor);
+                    del_old = dl;
+                    it++;
+                }
+            } else if (phase == AGAIN) {
+                if (!finite) {
+                    status = 4;
+                } else {
+                    z[1] = h * f;
 #pragma unroll
-                    for (int kk = kQmax; kk >= 1; kk--)
-#pragma unroll
-                        for (int j = kk; j <= kQmax; j++)
-                            if (j <= q && kk <= q) z[j - 1] -= z[j];
-                    netf++;
-                    if (++nef >= kMaxNef) {
-                        status = 2;
-                        break;
+                    for (int j = 0; j < kQmax + 2; j++) C.tau[j] = 0.0;
+                    qwait = 2;
+                    ehat_ok = false;
+                    new_attempt = true;
+                }
+            } else {
+                // ---------------- initial derivative and step ----------------
+                bool begin = false;
+                if (phase == FIRST) {
+                    f0 = f;
+                    h = t_end;
+                    if (!finite) {
+                        status = 4;
+                    } else if (wnorm(f0) == 0.0) {
+                        begin = true;
+                    } else {
+                        // hub = min over components of (0.1|y0| + 1/w)/|f0| where it binds
+                        const double af = active ? fabs(f0) : 0.0, lim = 0.1 * fabs(z[0]) + 1.0 / w;
+                        hub = -Gp::max(-(af * t_end > lim ? lim / af : t_end));
+                        hg = hub;
+                        it = 0;
+                        phase = STEP0;
                     }
-                    last = false;
-                    if (nef >= kNefRestart) {
-                        h *= kEtaMinEf;
-                        q = 1;
-                        const double fr = wave_rhs<NP, LT, G>(m, wt, L, sp, K, p, z[0], qbuf);
-                        nfe++;
-                        if (!all_finite(fr)) {
-                            status = 4;
-                            break;
-                        }
-                        z[1] = h * fr;
-#pragma unroll
-                        for (int j = 0; j < kQmax + 2; j++) tau[j] = 0.0;
-                        qwait = 2;
-                        ehat_ok = false;
-                        continue;
+                } else {
+                    bool done = false;
+                    if (!finite) {
+                        hg *= 0.1;
+                    } else {
+                        const double ydd = wnorm((f - f0) / hg);
+                        double hnew = ydd > 0.0 ? sqrt(2.0 / ydd) : hub;
+                        if (hnew > hub) hnew = hub;
+                        const double ratio = hnew / hg;
+                        hg = hnew;
+                        done = ratio >= 0.5 && ratio <= 2.0;
                     }
-                    double eta = 1.0 / (pow(kBiasQ * dsm, 1.0 / (q + 1)) + kAddon);
+                    if (done || ++it >= kH0Iters) {
+                        h = 0.5 * hg;
+                        if (h > t_end) h = t_end;
+                        begin = true;
+                    }
+                }
+                if (begin) {
+                    z[1] = h * f0;
+                    q = 1;
+                    qwait = 2;
+                    nst_M = 0;
+                    have_M = false;
+                    ehat_ok = false;
+                    gamma_M = 1.0;
+                    crate = 1.0;
+                    ehat_h = 0.0;
+                    ehat = 0.0;
+                    t = 0.0;
+#pragma unroll
+                    for (int j = 0; j < kQmax + 2; j++) C.tau[j] = 0.0;
+                    new_step = true;
+                }
+            }
+        }
+        if (fail && status == 0) {
+            unpredict();
+            new_attempt = true;
+            if (!jcur) {
+                force_M = true;
+            } else {
+                ncfn++;
+                if (++ncf >= kMaxNcf) status = 3;
+                rescale(kEtaCf);
+                h *= kEtaCf;
+                last = false;
+            }
+        }
+        if (conv) {
+            dsm = Cq * wnorm(e);
+            if (dsm > 1.0) {
+                unpredict();
+                netf++;
+                last = false;
+                if (++nef >= kMaxNef) {
+                    status = 2;
+                } else if (nef >= kNefRestart) {
+                    h *= kEtaMinEf;
+                    q = 1;
+                    phase = AGAIN;
+                } else {
+                    double eta = rcp_d(root_k(kBiasQ * dsm, q + 1) + kAddon);
                     eta = fmin(fmax(eta, kEtaMinEf), kEtaMaxEf);
                     if (nef >= 2) eta = fmin(eta, kEtaNef2);
-                    double f = 1.0;
-#pragma unroll
-                    for (int j = 1; j <= kQmax; j++) {
-                        f *= eta;
-                        if (j <= q) z[j] *= f;
-                    }
+                    rescale(eta);
                     h *= eta;
-                    continue;
+                    new_attempt = true;
                 }
-#pragma unroll
-                for (int j = 0; j <= kQmax; j++)
-                    if (j <= q) z[j] += l[j] * e;
-                break;
+                conv = false;
             }
-            if (status != 0) break;
+        }
+        if (conv) {
+            // ---------------- the step is accepted ----------------
+            with_order<UQ>(q, [&](auto Q) __attribute__((always_inline)) {
+                static_for<0, kQmax + 1>([&](auto j) __attribute__((always_inline)) {
+                    if (j <= Q) z[j] += C.l[j] * e;
+                });
+            });
             t = last ? t_end : t + h;
             nst++;
-            if (t >= t_end) break;
-
-            // ---------------- next step size and order ----------------
-            const double h_done = h;
-            double prod_q = 1.0;
-#pragma unroll
-            for (int i = 1; i <= kQmax; i++)
-                if (i <= q) prod_q *= xi[i];
-            double x1 = h;
-#pragma unroll
-            for (int i = 1; i <= kQmax; i++)
-                if (i <= q) x1 += tau[i];
-            x1 /= h;
-            double fact = 1.0;
-#pragma unroll
-            for (int i = 2; i <= kQmax + 1; i++)
-                if (i <= q + 1) fact *= i;
-            const double gfac = prod_q * (1.0 / l[1] + x1) / fact;
-            const double ehat_new = e / gfac;
-            if (qwait > 0) qwait--;
-            const double etamax = (nef > 0 || ncf > 0) ? 1.0 : (nst == 1 ? kEtaMaxFirst : kEtaMax);
-            double eta = 1.0;
-            int qnew = q;
-            if (etamax > 1.0) {
-                eta = 1.0 / (pow(kBiasQ * dsm, 1.0 / (q + 1)) + kAddon);
-                if (qwait == 0) {
-                    double eta_m = 0.0, eta_p = 0.0;
-                    if (q > 1) {
-                        double prod = 1.0, l1 = 0.0, zq = 0.0;
-#pragma unroll
-                        for (int j = 2; j <= kQmax; j++)
-                            if (j == q) zq = z[j];
-#pragma unroll
-                        for (int i = 1; i < kQmax; i++)
-                            if (i <= q - 1) {
-                                prod *= xi[i];
-                                l1 += 1.0 / xi[i];
-                            }
-                        const double Em = wnorm(zq) * prod / l1;
-                        eta_m = 1.0 / (pow(kBiasQm1 * Em, 1.0 / q) + kAddon);
+            new_step = true;
+            if (t < t_end) {
+                // ---------------- next step size and order ----------------
+                const double h_done = h;
+                const double ehat_new = e * (C.fact[q + 1] * rcp_d(C.pxi[q] * (inv_l1 + xq1)));
+                if (qwait > 0) qwait--;
+                const double etamax = (nef > 0 || ncf > 0) ? 1.0 : (nst == 1 ? kEtaMaxFirst : kEtaMax);
+                double eta = 1.0;
+                int qnew = q;
+                if (etamax > 1.0) {
+                    // step factors for the orders q, q - 1 and q + 1: lane i of the
+                    // group takes the root for the i-th, one evaluation for all
+                    double x = kBiasQ * dsm;
+                    int k = q + 1;
+                    const bool select = qwait == 0;
+                    const bool lower = select && q > 1, raise = select && q < io.prm->qmax && ehat_ok;
+                    if (lower) {
+                        const double zq = top_column();
+                        const double Em = wnorm(zq) * C.pxi[q - 1] * rcp_d(C.sxi[q - 1]);
+                        if (lane == 1) {
+                            x = kBiasQm1 * Em;
+                            k = q;
+                        }
                     }
-                    if (q < io.prm->qmax && ehat_ok) {
-                        const double rr = pow(h_done / ehat_h, q + 1);
-                        const double dv = ehat_new - ehat * rr;
-                        double prod = 1.0, l1 = 0.0;
-#pragma unroll
-                        for (int i = 1; i <= kQmax; i++)
-                            if (i <= q + 1) {
-                                prod *= xi[i];
-                                l1 += 1.0 / xi[i];
-                            }
-                        double fact2 = fact * (q + 2);
-                        const double Ep = wnorm(dv) * prod / (fact2 * l1);
-                        eta_p = 1.0 / (pow(kBiasQp1 * Ep, 1.0 / (q + 2)) + kAddon);
+                    if (raise) {
+                        const double dv = ehat_new - ehat * pow_k(h_done * rcp_d(ehat_h), q + 1);
+                        const double Ep = wnorm(dv) * C.pxi[q + 1] * rcp_d(C.fact[q + 2] * C.sxi[q + 1]);
+                        if (lane == 2) {
+                            x = kBiasQp1 * Ep;
+                            k = q + 2;
+                        }
                     }
-                    if (eta_m > eta && eta_m >= eta_p) {
-                        eta = eta_m;
-                        qnew = q - 1;
-                    } else if (eta_p > eta) {
-                        eta = eta_p;
-                        qnew = q + 1;
+                    const double er = rcp_d(root_k(x, k) + kAddon);
+                    eta = Gp::at_k(er, 0);
+                    if (select) {
+                        const double eta_m = lower ? Gp::at_k(er, 1) : 0.0, eta_p = raise ? Gp::at_k(er, 2) : 0.0;
+                        if (eta_m > eta && eta_m >= eta_p) {
+                            eta = eta_m;
+                            qnew = q - 1;
+                        } else if (eta_p > eta) {
+                            eta = eta_p;
+                            qnew = q + 1;
+                        }
+                    }
+                    if (eta < kThresh) {
+                        eta = 1.0;
+                        qnew = q;
+                    } else if (eta > etamax) {
+                        eta = etamax;
                     }
                 }
-                if (eta < kThresh) {
-                    eta = 1.0;
-                    qnew = q;
-                } else if (eta > etamax) {
-                    eta = etamax;
+                if (qnew == q - 1) {
+                    const double zq = top_column();
+                    with_order<UQ>(q, [&](auto Q) __attribute__((always_inline)) {
+                        double d[kQmax + 2];
+                        static_for<0, kQmax + 2>([&](auto j) __attribute__((always_inline)) { d[j] = 0.0; });
+                        d[1] = 1.0;
+                        static_for<1, kQmax>([&](auto i) __attribute__((always_inline)) {
+                            if (i <= Q - 1)
+                                static_for<0, decltype(i)::value + 1>([&](auto m) __attribute__((always_inline)) {
+                                    constexpr int j = decltype(i)::value + 1 - decltype(m)::value;
+                                    d[j] = d[j - 1] + C.xi[i] * d[j];
+                                });
+                        });
+                        static_for<1, kQmax>([&](auto j) __attribute__((always_inline)) {
+                            if (j < Q) z[j] -= d[j] * zq;
+                        });
+                    });
+                    q = qnew;
+                    qwait = q + 1;
+                    ehat_ok = false;
+                } else if (qnew == q + 1) {
+                    const double inv = rcp_d(xq1);
+                    with_order<UQ>(q, [&](auto Q) __attribute__((always_inline)) {
+                        static_for<1, kQmax + 1>([&](auto j) __attribute__((always_inline)) {
+                            if (j == Q + 1) z[j] = 0.0;
+                            if (j <= Q + 1) z[j] += e * C.l[j - 1] * inv;
+                        });
+                    });
+                    q = qnew;
+                    qwait = q + 1;
+                    ehat_ok = false;
+                } else {
+                    ehat = ehat_new;
+                    ehat_h = h_done;
+                    ehat_ok = true;
                 }
-            }
-            if (qnew == q - 1) {
-                double d[kQmax + 2];
 #pragma unroll
-                for (int j = 0; j < kQmax + 2; j++) d[j] = 0.0;
-                d[1] = 1.0;
-#pragma unroll
-                for (int i = 1; i < kQmax; i++)
-                    if (i <= q - 1)
-#pragma unroll
-                        for (int j = kQmax; j >= 1; j--)
-                            if (j <= i + 1) d[j] = d[j - 1] + xi[i] * d[j];
-                double zq = 0.0;
-#pragma unroll
-                for (int j = 2; j <= kQmax; j++)
-                    if (j == q) zq = z[j];
-#pragma unroll
-                for (int j = 1; j < kQmax; j++)
-                    if (j < q) z[j] -= d[j] * zq;
-                q = qnew;
-                qwait = q + 1;
-                ehat_ok = false;
-            } else if (qnew == q + 1) {
-                const double inv = 1.0 / x1;
-#pragma unroll
-                for (int j = 2; j <= kQmax; j++)
-                    if (j == q + 1) z[j] = 0.0;
-#pragma unroll
-                for (int j = 1; j <= kQmax; j++)
-                    if (j <= q + 1) z[j] += e * l[j - 1] * inv;
-                q = qnew;
-                qwait = q + 1;
-                ehat_ok = false;
-            } else {
-                ehat = ehat_new;
-                ehat_h = h_done;
-                ehat_ok = true;
-            }
-#pragma unroll
-            for (int i = kQmax + 1; i >= 2; i--) tau[i] = tau[i - 1];
-            tau[1] = h_done;
-            if (eta != 1.0) {
-                double f = 1.0;
-#pragma unroll
-                for (int j = 1; j <= kQmax; j++) {
-                    f *= eta;
-                    if (j <= q) z[j] *= f;
+                for (int i = kQmax + 1; i >= 2; i--) C.tau[i] = C.tau[i - 1];
+                C.tau[1] = h_done;
+                if (eta != 1.0) {
+                    rescale(eta);
+                    h *= eta;
                 }
-                h *= eta;
+                continue;
             }
-        } while (false);
-        if (status == 0 && t < t_end) continue;
+        } else if (status == 0) {
+            continue;
+        }
         // ---------------- the cell is done ----------------
         if (status == 0 && !all_finite(z[0])) status = 4;
         if (status == 0) {
@@ -982,39 +1057,67 @@ __device__ void run_cells(const DevMechView &m, const WaveTables &wt, const Cell
     }
 }
 
-// Reaction scratch of the right-hand side and the Jacobian (7 R doubles per
-// cell in flight): in LDS after `qlds` (QLDS), else a global slice per group
-// (qscratch).  Fixing the choice at compile time keeps LDS accesses as LDS
-// instructions.
-template <int NP, typename LT, int G, bool QLDS, bool DEFER>
-__device__ __forceinline__ void run_block(const DevMechView &m, const WaveTables &wt, double *T, const double *p,
-                                          double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
-                                          int32_t *status, int32_t *counters, unsigned long long *queue,
-                                          double *qscratch, double *qlds, WaveLds<NP, LT, G> *Ls)
+// One 64-lane wave per cell.  Two waves per SIMD: with 256 registers each
+// row of the inverse, the Nordsieck column and the rates in flight stay in
+// registers, and the second wave covers part of the first one's latencies.
+template <int NP, typename LT, int RPL, bool QLDS>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
+bdf_wave_kernel(DevMechView m, Wave64Tables wt, double *__restrict__ T, const double *__restrict__ p,
+                double *__restrict__ Y, int64_t ldY, int64_t n, double dt, BdfParams prm,
+                int32_t *__restrict__ status, int32_t *__restrict__ counters,
+                unsigned long long *__restrict__ queue, double *__restrict__ qscratch)
+{
+    __shared__ Wave64Lds<NP, LT> L;
+    __shared__ StepLds C;
+    extern __shared__ double dyn[];
+    const CellIO io = make_cell_io(T, p, Y, ldY, n, status, counters, prm);
+    if constexpr (QLDS) {
+        WaveSys<NP, LT, RPL, true> S(m, wt, L, dyn);
+        run_cells<WaveSys<NP, LT, RPL, true>, false>(S, C, io, dt, queue);
+    } else {
+        WaveSys<NP, LT, RPL, false> S(m, wt, L, qscratch + (size_t)blockIdx.x * m.qstride);
+        run_cells<WaveSys<NP, LT, RPL, false>, false>(S, C, io, dt, queue);
+    }
+}
+
+// One wave per cell of a mechanism that fits the tile (N <= 16): the tile's
+// operations in the tile's order, so that the two schedules agree bit for bit.
+template <typename LT>
+__global__ void __launch_bounds__(64) bdf_small_wave_kernel(DevMechView m, WaveTables wt, double *__restrict__ T,
+                                                            const double *__restrict__ p, double *__restrict__ Y,
+                                                            int64_t ldY, int64_t n, double dt, BdfParams prm,
+                                                            int32_t *__restrict__ status,
+                                                            int32_t *__restrict__ counters,
+                                                            unsigned long long *__restrict__ queue,
+                                                            double *__restrict__ qscratch)
+{
+    __shared__ WaveLds<16, LT, 64> L;
+    __shared__ StepLds C;
+    extern __shared__ double dyn[];
+    const CellIO io = make_cell_io(T, p, Y, ldY, n, status, counters, prm);
+    GroupSys<16, LT, 64> S(m, wt, L, dyn);
+    run_cells<GroupSys<16, LT, 64>, false>(S, C, io, dt, queue);
+}
+
+// The tile's reaction scratch (7 R doubles per cell in flight): in LDS after
+// `qlds` (QLDS), else a global slice per group (qscratch).  Fixing the choice
+// at compile time keeps LDS accesses as LDS instructions.
+template <int NP, typename LT, bool QLDS, bool DEFER>
+__device__ __forceinline__ void run_tile(const DevMechView &m, const WaveTables &wt, double *T, const double *p,
+                                         double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
+                                         int32_t *status, int32_t *counters, unsigned long long *queue,
+                                         double *qscratch, double *qlds, WaveLds<NP, LT, 16> *Ls, StepLds *Cs)
 {
     const CellIO io = make_cell_io(T, p, Y, ldY, n, status, counters, prm);
-    const int slot = Grp<G>::slot();
+    const int slot = Grp<16>::slot();
     const size_t q7 = (size_t)m.qstride;
     double *qbuf;
     if constexpr (QLDS)
         qbuf = qlds + slot * q7;
     else
-        qbuf = qscratch + ((size_t)blockIdx.x * Grp<G>::kCells + slot) * q7;
-    run_cells<NP, LT, G, DEFER>(m, wt, io, dt, queue, qbuf, Ls[slot]);
-}
-
-// One 64-lane wave per cell.
-template <int NP, typename LT, bool QLDS>
-__global__ void __launch_bounds__(64) bdf_wave_kernel(DevMechView m, WaveTables wt, double *__restrict__ T,
-                                                      const double *__restrict__ p, double *__restrict__ Y,
-                                                      int64_t ldY, int64_t n, double dt, BdfParams prm,
-                                                      int32_t *__restrict__ status, int32_t *__restrict__ counters,
-                                                      unsigned long long *__restrict__ queue,
-                                                      double *__restrict__ qscratch)
-{
-    __shared__ WaveLds<NP, LT, 64> Ls[1];
-    extern __shared__ double dyn[];
-    run_block<NP, LT, 64, QLDS, false>(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch, dyn, Ls);
+        qbuf = qscratch + ((size_t)blockIdx.x * 4 + slot) * q7;
+    GroupSys<NP, LT, 16> S(m, wt, Ls[slot], qbuf);
+    run_cells<GroupSys<NP, LT, 16>, DEFER>(S, Cs[slot], io, dt, queue);
 }
 
 // Tile schedule: 16 lanes per cell, four cells per wave (N <= NP <= 16).  With
@@ -1032,6 +1135,7 @@ __global__ void __launch_bounds__(64) bdf_tile_kernel(DevMechView m, WaveTables 
                                                       double *__restrict__ qscratch)
 {
     __shared__ WaveLds<NP, LT, 16> Ls[4];
+    __shared__ StepLds Cs[4];
     extern __shared__ double dyn[];
     if constexpr (STAGE) {
         const int tb = m.table_bytes;
@@ -1050,11 +1154,11 @@ __global__ void __launch_bounds__(64) bdf_tile_kernel(DevMechView m, WaveTables 
         WaveTables wl;
         wl.inc_off = (const int *)(lds + ((const char *)wt.inc_off - base));
         wl.inc = (const int2 *)(lds + ((const char *)wt.inc - base));
-        run_block<NP, LT, 16, true, DEFER>(ml, wl, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch,
-                                           dyn + tb / 8, Ls);
+        run_tile<NP, LT, true, DEFER>(ml, wl, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch,
+                                           dyn + tb / 8, Ls, Cs);
     } else {
-        run_block<NP, LT, 16, false, DEFER>(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch, dyn,
-                                            Ls);
+        run_tile<NP, LT, false, DEFER>(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch, dyn,
+                                           Ls, Cs);
     }
 }
 
@@ -1068,9 +1172,9 @@ int wave_kernel_rows(int N) { return N <= 16 ? 16 : (N <= 40 ? 40 : (N <= 64 ? 6
 // (occupancy with `dyn` bytes of dynamic LDS), at most one per `cells_per_wave`
 // cells, at most max_groups / cells_per_wave when the reaction scratch is in
 // global memory (one slice per group).
-template <typename Kern>
+template <typename Kern, typename Tables>
 static hipError_t launch_groups(Kern kern, int cells_per_wave, size_t dyn, bool qglobal, const DevMechView &m,
-                                const WaveTables &wt, double *T, const double *p, double *Y, int64_t ldY, int64_t n,
+                                const Tables &wt, double *T, const double *p, double *Y, int64_t ldY, int64_t n,
                                 double dt, const BdfParams &prm, int32_t *status, int32_t *counters,
                                 unsigned long long *queue, double *qscratch, int max_groups, hipStream_t s)
 {
@@ -1096,31 +1200,45 @@ static hipError_t launch_groups(Kern kern, int cells_per_wave, size_t dyn, bool 
     return hipGetLastError();
 }
 
-constexpr size_t kQbufLdsMax = 49152;     // reaction scratch of one wave kept in LDS up to this size
+constexpr size_t kWaveLdsMax = 49152;     // reaction scratch of one wave kept in LDS up to this size
 constexpr size_t kTileStageMax = 24576;   // tables + scratch of a tile block staged in LDS up to this size
 constexpr int64_t kDeferMinCells = 65536; // tile batches from this size defer Newton-matrix refreshes
+
+// Reactions per lane the wave kernel holds in registers (0: more than 4).
+static int wave_regs(int R) { return R <= 128 ? 2 : R <= 256 ? 4 : 0; }
+
+// Whether the wave schedule runs the tile's operations (bdf_small_wave_kernel).
+static bool wave_small(const DevMechView &m)
+{
+    return m.K + 1 <= 16 && (size_t)m.qstride * sizeof(double) <= kWaveLdsMax;
+}
+
+// Bytes of the wave kernel's scratch (layout in wave_tables.h and
+// wave_system.h): at most qstride doubles.
+static size_t wave_scratch_bytes(const DevMechView &m)
+{
+    if (wave_small(m)) return (size_t)m.qstride * sizeof(double);
+    const size_t per = 4 + (m.n_pdep ? 1 : 0) + (wave_regs(m.R) ? 0 : 2);
+    return (per * m.R + 1) * sizeof(double);
+}
 
 #if !CHEM_WAVE_PDEP
 bool wave_uses_global_scratch(const DevMechView &m, int lanes)
 {
     const size_t q7 = (size_t)m.qstride * sizeof(double);
     if (lanes == 16) return (size_t)m.table_bytes + 4 * q7 > kTileStageMax;
-    return q7 > kQbufLdsMax;
+    return wave_scratch_bytes(m) > kWaveLdsMax;
 }
 #endif
 
-template <int NP, typename LT>
-static hipError_t launch_wave(const DevMechView &m, const WaveTables &wt, double *T, const double *p, double *Y,
+template <int NP, int RPL, typename LT, bool QLDS = true>
+static hipError_t launch_wave(const DevMechView &m, const Wave64Tables &wt, double *T, const double *p, double *Y,
                               int64_t ldY, int64_t n, double dt, const BdfParams &prm, int32_t *status,
                               int32_t *counters, unsigned long long *queue, double *qscratch, int max_groups,
                               hipStream_t s)
 {
-    const size_t qbytes = (size_t)m.qstride * sizeof(double);
-    if (qbytes <= kQbufLdsMax)
-        return launch_groups(bdf_wave_kernel<NP, LT, true>, 1, qbytes, false, m, wt, T, p, Y, ldY, n, dt, prm,
-                             status, counters, queue, qscratch, max_groups, s);
-    return launch_groups(bdf_wave_kernel<64, LT, false>, 1, 0, true, m, wt, T, p, Y, ldY, n, dt, prm, status,
-                         counters, queue, qscratch, max_groups, s);
+    return launch_groups(bdf_wave_kernel<NP, LT, RPL, QLDS>, 1, QLDS ? wave_scratch_bytes(m) : 0, !QLDS, m, wt, T, p,
+                         Y, ldY, n, dt, prm, status, counters, queue, qscratch, max_groups, s);
 }
 
 template <int NP, typename LT>
@@ -1148,41 +1266,65 @@ static hipError_t launch_tile(const DevMechView &m, const WaveTables &wt, double
 }
 
 #if CHEM_WAVE_PDEP
-hipError_t launch_bdf_wave_pdep(const DevMechView &m, const WaveTables &wt, double *T, const double *p,
-                                double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
+hipError_t launch_bdf_wave_pdep(const DevMechView &m, const WaveTables &wt, const Wave64Tables &w64, double *T,
+                                const double *p, double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
                                 int32_t *status, int32_t *counters, unsigned long long *queue,
                                 double *qscratch, int max_groups, bool fp32_lu, int lanes, hipStream_t s)
 {
 #else
-hipError_t launch_bdf_wave_pdep(const DevMechView &m, const WaveTables &wt, double *T, const double *p,
-                                double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
+hipError_t launch_bdf_wave_pdep(const DevMechView &m, const WaveTables &wt, const Wave64Tables &w64, double *T,
+                                const double *p, double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
                                 int32_t *status, int32_t *counters, unsigned long long *queue,
                                 double *qscratch, int max_groups, bool fp32_lu, int lanes, hipStream_t s);
 
-hipError_t launch_bdf_wave(const DevMechView &m, const WaveTables &wt, double *T, const double *p,
-                           double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
+hipError_t launch_bdf_wave(const DevMechView &m, const WaveTables &wt, const Wave64Tables &w64, double *T,
+                           const double *p, double *Y, int64_t ldY, int64_t n, double dt, const BdfParams &prm,
                            int32_t *status, int32_t *counters, unsigned long long *queue,
                            double *qscratch, int max_groups, bool fp32_lu, int lanes, hipStream_t s)
 {
     if (m.n_pdep)
-        return launch_bdf_wave_pdep(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch,
+        return launch_bdf_wave_pdep(m, wt, w64, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch,
                                     max_groups, fp32_lu, lanes, s);
 #endif
-#define CHEM_LAUNCH(FN, NPV)                                                                                     \
-    return fp32_lu ? FN<NPV, float>(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch,        \
-                                    max_groups, s)                                                             \
-                   : FN<NPV, double>(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch,       \
-                                     max_groups, s)
+#define CHEM_TILE_LAUNCH(NPV)                                                                                   \
+    return fp32_lu ? launch_tile<NPV, float>(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch, \
+                                             max_groups, s)                                                      \
+                   : launch_tile<NPV, double>(m, wt, T, p, Y, ldY, n, dt, prm, status, counters, queue, qscratch, \
+                                              max_groups, s)
+#define CHEM_WAVE_LAUNCH(NPV, RPL, ...)                                                                              \
+    return fp32_lu ? launch_wave<NPV, RPL, float __VA_ARGS__>(m, w64, T, p, Y, ldY, n, dt, prm, status, counters,    \
+                                                              queue, qscratch, max_groups, s)                        \
+                   : launch_wave<NPV, RPL, double __VA_ARGS__>(m, w64, T, p, Y, ldY, n, dt, prm, status, counters,   \
+                                                               queue, qscratch, max_groups, s)
     const int N = m.K + 1;
     if (lanes == 16) {
-        if (N <= 12) CHEM_LAUNCH(launch_tile, 12);
-        if (N <= 16) CHEM_LAUNCH(launch_tile, 16);
+        if (N <= 12) CHEM_TILE_LAUNCH(12);
+        if (N <= 16) CHEM_TILE_LAUNCH(16);
         return hipErrorInvalidValue;
     }
-    if (N <= 16) CHEM_LAUNCH(launch_wave, 16);
-    if (N <= 40) CHEM_LAUNCH(launch_wave, 40);
-    if (N <= 64) CHEM_LAUNCH(launch_wave, 64);
-#undef CHEM_LAUNCH
+    // the smallest built row count and number of reactions per lane that hold
+    // the mechanism: the inversion costs N x rows, a padded reaction as much
+    // as a real one
+    if (wave_small(m)) {
+        const size_t dyn = wave_scratch_bytes(m);
+        return fp32_lu ? launch_groups(bdf_small_wave_kernel<float>, 1, dyn, false, m, wt, T, p, Y, ldY, n, dt, prm,
+                                       status, counters, queue, qscratch, max_groups, s)
+                       : launch_groups(bdf_small_wave_kernel<double>, 1, dyn, false, m, wt, T, p, Y, ldY, n, dt, prm,
+                                       status, counters, queue, qscratch, max_groups, s);
+    }
+    const int rpl = wave_regs(m.R);
+    if (rpl == 0) {
+        if (wave_scratch_bytes(m) > kWaveLdsMax) CHEM_WAVE_LAUNCH(64, 0, , false);
+        if (N <= 48) CHEM_WAVE_LAUNCH(48, 0);
+        if (N <= 64) CHEM_WAVE_LAUNCH(64, 0);
+        return hipErrorInvalidValue;
+    }
+    if (N <= 24 && rpl <= 2) CHEM_WAVE_LAUNCH(24, 2);
+    if (N <= 36) CHEM_WAVE_LAUNCH(36, 4);
+    if (N <= 48) CHEM_WAVE_LAUNCH(48, 4);
+    if (N <= 64) CHEM_WAVE_LAUNCH(64, 4);
+#undef CHEM_WAVE_LAUNCH
+#undef CHEM_TILE_LAUNCH
     return hipErrorInvalidValue;
 }
 

@@ -235,7 +235,7 @@ int integrate_cells(chem_mech m, double *T, const double *p, double *Y, int64_t 
             const unsigned part = __atomic_fetch_add(&m->next_part, 1u, __ATOMIC_RELAXED) % kScratchParts;
             qs = m->wave_scratch + (size_t)part * m->wave_slots * m->view.qstride;
         }
-        e = chem::launch_bdf_wave(m->view, m->wave, T, p, Y, ldY, n, dt, prm, status, counters, queue, qs,
+        e = chem::launch_bdf_wave(m->view, m->wave, m->wave64, T, p, Y, ldY, n, dt, prm, status, counters, queue, qs,
                                   m->wave_slots, o.precision == 1, lanes, stream);
     }
     else {
@@ -377,7 +377,7 @@ int chem_load_mechanism(const char *path, int device, chem_mech *out)
     m->W = W;
     // one device block: the tables (species | W | invW | reactions | incidence
     // offsets | incidence entries, contiguous so that a kernel can copy them
-    // into LDS in one pass), then the work-queue counters, then wave scratch
+    // into LDS in one pass), then the work-queue counters, the wave tables and the wave scratch
     const size_t n_sp = species.size() * sizeof(double);
     const size_t n_w = (size_t)K * sizeof(double);
     auto a16 = [](size_t x) { return (x + 15) & ~size_t(15); };
@@ -408,7 +408,12 @@ int chem_load_mechanism(const char *path, int device, chem_mech *out)
     const size_t off_aux = a16(off_inc + inc_flat.size() * sizeof(int));
     const size_t table_bytes = a16(off_aux + aux.size() * sizeof(double));
     const size_t off_q = (table_bytes + 255) & ~size_t(255);
-    const size_t off_ws = off_q + kQueues * 256;
+    // then the wave kernel's own tables (K <= 63)
+    const size_t off_wt = off_q + kQueues * 256;
+    std::vector<char> wtab;
+    if (chem::wave_kernel_rows(K + 1) > 0)
+        wtab = chem::build_wave_tables(K, rx, R, inc_lists, species, W, aux, nullptr, m->wave64);
+    const size_t off_ws = (off_wt + wtab.size() + 255) & ~size_t(255);
     // global reaction scratch, only when a wave or tile variant needs it:
     // kScratchParts partitions of up to 4096 slices (cells in flight)
     chem::DevMechView probe{};
@@ -451,6 +456,10 @@ int chem_load_mechanism(const char *path, int device, chem_mech *out)
     std::memcpy(staging.data() + off_io, inc_off.data(), inc_off.size() * sizeof(int));
     std::memcpy(staging.data() + off_inc, inc_flat.data(), inc_flat.size() * sizeof(int));
     std::memcpy(staging.data() + off_aux, aux.data(), aux.size() * sizeof(double));
+    if (!wtab.empty()) {
+        chem::build_wave_tables(K, rx, R, inc_lists, species, W, aux, blk + off_wt, m->wave64);
+        std::memcpy(staging.data() + off_wt, wtab.data(), wtab.size());
+    }
     rc = check_hip(hipMemcpy(blk, staging.data(), off_ws, hipMemcpyHostToDevice), "hipMemcpy");
     hipSetDevice(prev);
     if (rc != CHEM_OK) {

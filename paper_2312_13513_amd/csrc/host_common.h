@@ -79,7 +79,8 @@ struct chem_mech_s {
     unsigned next_queue = 0;
     const chem::GenEntry *gen = nullptr;    // mechanism-specialised kernels, if compiled
     std::string variant = "table";
-    chem::WaveTables wave{};                // species -> reaction incidence (wave kernel)
+    chem::WaveTables wave{};                // species -> reaction incidence (tile kernel)
+    chem::Wave64Tables wave64{};            // lane-by-lane tables of the wave kernel
     // reaction scratch of the kernels whose 7 R doubles per cell in flight do
     // not fit in LDS: kScratchParts partitions of wave_slots slices, one
     // partition per call in rotation (NULL when no variant needs it)
