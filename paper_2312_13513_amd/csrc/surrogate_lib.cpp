@@ -12,6 +12,7 @@
 
 #include "host_common.h"
 #include "surrogate.h"
+#include "surrogate_train.h"
 #include "surr_file.h"
 
 using chem::bf16_t;
@@ -65,6 +66,11 @@ struct chem_surr_s {
     bf16_t *wbf = nullptr;
     bf16_t *wfrag = nullptr;          // the BF16 weights in the fused kernel's fragment order
     bool frag_valid = false;          // wfrag matches wbf
+    bf16_t *wfragT = nullptr;         // the transposes of layers 2..4 in that order (training, see train_fused)
+    int64_t off_T[4] = {0, 0, 0, 0};
+    bool fragT_valid = false;         // wfragT matches wbf
+    DevBuf tr;                        // activations and errors of a batch (train_fused)
+    int64_t tr_rows = 0;
     double *norm_dev = nullptr;       // mu_x, sig_x, mu_y, sig_y
     double *coef_dev = nullptr;       // [E][K] n_ke / W_k, then [K] R / W_k
     int64_t *scalars = nullptr;       // [0] fallback count
@@ -295,6 +301,118 @@ hipError_t backward(const chem_surr_s *s, const Acts &a, const bf16_t *X, int ro
     return e;
 }
 
+// Whether training runs the fused kernels (surrogate_train.hip).
+bool train_fused(const chem_surr_s *s) { return s->G == 1 && chem::train_fused_supported(s->in_l, s->out_l); }
+
+// Their workspace for batches of up to tr_rows rows (a multiple of 32).
+struct TrainBuf {
+    bf16_t *Xt, *Ht[3], *Dt[4];
+    double *loss_part;
+};
+
+TrainBuf carve_train(const chem_surr_s *s, int64_t rows, char *base, size_t &bytes)
+{
+    TrainBuf b{};
+    Carver c{base};
+    b.Xt = c.take<bf16_t>(rows * kInPad);
+    for (int l = 0; l < 3; l++) b.Ht[l] = c.take<bf16_t>(rows * s->out_l[l]);
+    for (int l = 0; l < 4; l++) b.Dt[l] = c.take<bf16_t>(rows * s->out_l[l]);
+    b.loss_part = c.take<double>(rows / 16);
+    bytes = c.off;
+    return b;
+}
+
+int ensure_train(chem_surr_s *s, int64_t rows, hipStream_t st)
+{
+    rows = (rows + 31) & ~int64_t(31);
+    if (rows <= s->tr_rows) return CHEM_OK;
+    size_t bytes = 0;
+    carve_train(s, rows, nullptr, bytes);
+    const int rc = s->tr.grow(bytes, st);
+    if (rc == CHEM_OK) s->tr_rows = rows;
+    return rc;
+}
+
+chem::UpdateArgs update_args(const chem_surr_s *s)
+{
+    chem::UpdateArgs u{};
+    u.n_pad = s->n_pad;
+    u.o.p = s->master;
+    u.wbf = s->wbf;
+    u.wfrag = s->wfrag;
+    u.wfragT = s->wfragT;
+    for (int l = 0; l < 4; l++) {
+        u.in_l[l] = s->in_l[l];
+        u.out_l[l] = s->out_l[l];
+        u.off_W[l] = s->off_W[l];
+        u.off_T[l] = s->off_T[l];
+    }
+    return u;
+}
+
+// Loss (added to loss_dev[0]) and gradient of `rows` rows of X; with `adam`
+// also its step and the BF16 weights, else the gradient stays in s->grad.
+hipError_t train_batch(chem_surr_s *s, const bf16_t *X, const int32_t *order, int64_t start, int64_t rows,
+                       const float *Y, int64_t ldy, const chem::AdamArgs *adam, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    if (!s->frag_valid || !s->fragT_valid) {
+        chem::UpdateArgs u = update_args(s);
+        u.weights = 1;
+        e = chem::launch_train_update(u, st);
+        if (e != hipSuccess) return e;
+        s->frag_valid = s->fragT_valid = true;
+    }
+    size_t bytes = 0;
+    const TrainBuf b = carve_train(s, s->tr_rows, (char *)s->tr.p, bytes);
+    chem::TrainArgs t{};
+    t.X = X;
+    t.order = order;
+    t.start = start;
+    t.rows = rows;
+    t.Y = Y;
+    t.ldy = ldy;
+    t.K = s->K;
+    t.scale = 2.0f / ((float)rows * (float)s->K);
+    t.Xt = b.Xt;
+    t.ldT = s->tr_rows;
+    t.loss_part = b.loss_part;
+    chem::GradArgs g{};
+    g.Xt = b.Xt;
+    g.ldT = s->tr_rows;
+    g.rows = rows;
+    g.g = s->grad;
+    for (int l = 0; l < 4; l++) {
+        t.W[l] = s->wfrag + s->off_W[l];
+        if (l > 0) t.WT[l - 1] = s->wfragT + s->off_T[l];
+        t.b[l] = s->master + s->off_b[l];
+        t.in_l[l] = g.in_l[l] = s->in_l[l];
+        t.out_l[l] = g.out_l[l] = s->out_l[l];
+        t.Dt[l] = b.Dt[l];
+        g.Dt[l] = b.Dt[l];
+        if (l < 3) {
+            t.Ht[l] = b.Ht[l];
+            g.Ht[l] = b.Ht[l];
+        }
+        g.tiles[l] = (s->out_l[l] + 31) / 32 * (s->in_l[l] / 32);
+        g.all_tiles += g.tiles[l];
+        g.off_W[l] = s->off_W[l];
+        g.off_b[l] = s->off_b[l];
+    }
+    e = chem::launch_train_rows(t, st);
+    if (e == hipSuccess) e = chem::launch_train_grad(g, st);
+    if (e != hipSuccess) return e;
+    chem::UpdateArgs u = update_args(s);
+    u.loss_part = b.loss_part;
+    u.loss_blocks = (int)((rows + 15) / 16);
+    u.loss = s->loss_dev;
+    if (adam) {
+        u.weights = u.adam = 1;
+        u.o = *adam;
+    }
+    return chem::launch_train_update(u, st);
+}
+
 // logical <-> padded parameter vectors
 void logical_map(const chem_surr_s *s, std::vector<std::pair<int64_t, int64_t>> &runs)
 {
@@ -357,7 +475,7 @@ int download_logical(chem_surr_s *s, const float *dev, float *host, int64_t coun
 
 int refresh_bf16(chem_surr_s *s, hipStream_t st)
 {
-    s->frag_valid = false;
+    s->frag_valid = s->fragT_valid = false;
     return check_hip(chem::launch_to_bf16(s->master, s->wbf, s->n_pad, st), "bf16 weights");
 }
 
@@ -505,8 +623,15 @@ int create_surrogate(chem_mech mech, int32_t h1, int32_t h2, int32_t h3, bool pe
         s->n_logical = (int64_t)G * ((int64_t)s->nin * hr[0] + hr[0] + (int64_t)hr[0] * hr[1] + hr[1] +
                                      (int64_t)hr[1] * hr[2] + hr[2] + hr[2] + 1);
     s->n_pad = off;
+    // transposes of layers 2..4 for training, columns padded to 64 (zeros)
+    int64_t n_T = 0;
+    if (train_fused(s))
+        for (int l = 1; l < 4; l++) {
+            s->off_T[l] = n_T;
+            n_T += (int64_t)in_l[l] * round_up(out_l[l], 64);
+        }
     const int64_t nn = 2 * (int64_t)s->nin + 2 * K;
-    const size_t bytes = 4 * carve_size<float>(s->n_pad) + 2 * carve_size<bf16_t>(s->n_pad) +
+    const size_t bytes = 4 * carve_size<float>(s->n_pad) + 2 * carve_size<bf16_t>(s->n_pad) + carve_size<bf16_t>(n_T) +
                          carve_size<double>(nn) + carve_size<double>((int64_t)(E + 1) * K) +
                          carve_size<int64_t>(8) + carve_size<double>(80);
     if (hipMalloc(&s->block, bytes) != hipSuccess) {
@@ -522,6 +647,7 @@ int create_surrogate(chem_mech mech, int32_t h1, int32_t h2, int32_t h3, bool pe
     s->av = c.take<float>(s->n_pad);
     s->wbf = c.take<bf16_t>(s->n_pad);
     s->wfrag = c.take<bf16_t>(s->n_pad);
+    s->wfragT = c.take<bf16_t>(n_T);
     s->norm_dev = c.take<double>(nn);
     s->coef_dev = c.take<double>((int64_t)(E + 1) * K);
     s->scalars = c.take<int64_t>(8);
@@ -579,6 +705,7 @@ void chem_free_surrogate(chem_surr s)
     hipGetDevice(&prev);
     hipSetDevice(s->device);
     s->act.release();
+    s->tr.release();
     s->fb.release();
     s->io.release();
     s->pcount.release();
@@ -913,21 +1040,28 @@ int chem_surrogate_grad(chem_surr s, const uint16_t *X, const float *Yt, int64_t
     if (n < 1 || n > (1 << 20) || ldt < s->K) return fail(CHEM_EINVAL, "need 1 <= n <= 2^20 and ldt >= K");
     if (!is_device_ptr(X) || !is_device_ptr(Yt)) return fail(CHEM_EINVAL, "X and Yt must be device pointers");
     hipStream_t st = (hipStream_t)stream;
-    rc = ensure_acts(s, n, true, st);
-    if (rc != CHEM_OK) return rc;
-    Acts a = carve_acts(s);
-    // targets into the padded layout
-    rc = check_hip(hipMemsetAsync(a.Yb, 0, (size_t)n * s->nout_pad * sizeof(float), st), "clear");
-    if (rc != CHEM_OK) return rc;
-    rc = check_hip(hipMemcpy2DAsync(a.Yb, (size_t)s->nout_pad * sizeof(float), Yt, (size_t)ldt * sizeof(float),
-                                    (size_t)s->K * sizeof(float), (size_t)n, hipMemcpyDeviceToDevice, st),
-                   "targets");
+    const bool fused = train_fused(s) && (uintptr_t)X % 16 == 0;
+    rc = fused ? ensure_train(s, n, st) : ensure_acts(s, n, true, st);
     if (rc != CHEM_OK) return rc;
     rc = check_hip(hipMemsetAsync(s->loss_dev, 0, sizeof(double), st), "clear");
     if (rc != CHEM_OK) return rc;
-    hipError_t e = forward(s, X, (int)n, a.H, a.U, a.OUT, s->nout_pad, st);
-    if (e == hipSuccess) e = chem::launch_loss_grad(a.OUT, a.Yb, (int)n, s->K, s->nout_pad, a.dOut, s->loss_dev, st);
-    if (e == hipSuccess) e = backward(s, a, X, (int)n, st);
+    hipError_t e;
+    if (fused) {
+        e = train_batch(s, (const bf16_t *)X, nullptr, 0, n, Yt, ldt, nullptr, st);
+    } else {
+        Acts a = carve_acts(s);
+        // targets into the padded layout
+        rc = check_hip(hipMemsetAsync(a.Yb, 0, (size_t)n * s->nout_pad * sizeof(float), st), "clear");
+        if (rc != CHEM_OK) return rc;
+        rc = check_hip(hipMemcpy2DAsync(a.Yb, (size_t)s->nout_pad * sizeof(float), Yt, (size_t)ldt * sizeof(float),
+                                        (size_t)s->K * sizeof(float), (size_t)n, hipMemcpyDeviceToDevice, st),
+                       "targets");
+        if (rc != CHEM_OK) return rc;
+        e = forward(s, X, (int)n, a.H, a.U, a.OUT, s->nout_pad, st);
+        if (e == hipSuccess)
+            e = chem::launch_loss_grad(a.OUT, a.Yb, (int)n, s->K, s->nout_pad, a.dOut, s->loss_dev, st);
+        if (e == hipSuccess) e = backward(s, a, X, (int)n, st);
+    }
     if (e != hipSuccess) return check_hip(e, "gradient");
     double acc = 0.0;
     rc = check_hip(hipMemcpyAsync(&acc, s->loss_dev, sizeof(double), hipMemcpyDeviceToHost, st), "loss");
@@ -987,7 +1121,8 @@ int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, con
         return fail(CHEM_EINVAL, "arrays must be device pointers");
     hipStream_t st = (hipStream_t)stream;
     const int64_t rows = batch < n ? batch : n;
-    rc = ensure_acts(s, rows, true, st);
+    const bool fused = train_fused(s);
+    rc = fused ? ensure_train(s, rows, st) : ensure_acts(s, rows, true, st);
     if (rc != CHEM_OK) return rc;
     DevBuf data;
     rc = data.grow(carve_size<bf16_t>(n * kInPad) + carve_size<float>(n * s->nout_pad), st);
@@ -995,7 +1130,7 @@ int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, con
     Carver dc{(char *)data.p};
     bf16_t *Xall = dc.take<bf16_t>(n * kInPad);
     float *Yall = dc.take<float>(n * s->nout_pad);
-    Acts a = carve_acts(s);
+    Acts a = fused ? Acts{} : carve_acts(s);
     hipError_t e = chem::launch_encode(T, p, Y, ldY, n, s->K, kInPad, s->norm_dev, Xall, st);
     if (e == hipSuccess)
         e = chem::launch_targets(Y, ldY, Yn, ldYn, n, s->K, s->nout_pad, s->norm_dev + 2 * s->nin,
@@ -1008,6 +1143,14 @@ int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, con
         for (int64_t b = 0; b < per_epoch && e == hipSuccess; b++, step++) {
             const int64_t start = b * batch;
             const int rr = (int)(n - start < batch ? n - start : batch);
+            const double lr = lr1 + 0.5 * (lr0 - lr1) * (1.0 + std::cos(kPi * (double)step / (double)total));
+            if (fused) {
+                s->adam_t++;
+                const chem::AdamArgs aa = adam_args(s, lr);
+                e = train_batch(s, Xall, order ? order + (int64_t)ep * n : nullptr, start, rr, Yall, s->nout_pad, &aa,
+                                st);
+                continue;
+            }
             e = chem::launch_gather_rows(order ? order + (int64_t)ep * n : nullptr, start, rr, Xall, kInPad,
                                          Yall, s->nout_pad, a.X, a.Yb, st);
             if (e == hipSuccess) e = forward(s, a.X, rr, a.H, a.U, a.OUT, s->nout_pad, st);
@@ -1015,11 +1158,10 @@ int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, con
                 e = chem::launch_loss_grad(a.OUT, a.Yb, rr, s->K, s->nout_pad, a.dOut, s->loss_dev, st);
             if (e == hipSuccess) e = backward(s, a, a.X, rr, st);
             if (e == hipSuccess) {
-                const double lr = lr1 + 0.5 * (lr0 - lr1) * (1.0 + std::cos(kPi * (double)step / (double)total));
                 s->adam_t++;
                 e = chem::launch_adam(adam_args(s, lr), st);
                 if (e == hipSuccess) e = chem::launch_to_bf16(s->master, s->wbf, s->n_pad, st);
-                s->frag_valid = false;
+                s->frag_valid = s->fragT_valid = false;
             }
         }
         if (e == hipSuccess && loss_per_epoch) {
