@@ -383,8 +383,8 @@ int chem_surrogate_apply(chem_surr surr, double *T, const double *p, double *Y, 
  * status (nullable): integrator status of fallback cells, 0 elsewhere.
  * fallback_count (nullable, device int64): number of fallback cells.
  * dt must equal the dt of the normalisation.  The cells run in passes; the
- * rejected cells of each pass are integrated on the handle's own second
- * stream (default priority) while the later passes run, joined back into
+ * rejected cells of each pass are integrated on one of the handle's own side
+ * streams (default priority) while the later passes run, joined back into
  * hip_stream by events before the call's last kernel, so the call stays
  * asynchronous and capturable. */
 int chem_surrogate_infer(chem_surr surr, double *T, const double *p, double *Y, int64_t ldY,
