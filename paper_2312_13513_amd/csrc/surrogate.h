@@ -46,6 +46,25 @@ struct GemmArgs {
 
 hipError_t launch_gemm_bf16(const GemmArgs &g, hipStream_t s);
 
+// One GELU layer of inference, `groups` networks side by side: rows of N units
+// H[m][z N + n] = bf16(gelu(sum_k A[m][z za + k] W_z[n][k] + bias[z N + n])), W in
+// fragment order (launch_swizzle_frag of the [groups N][K] matrix).  N and K
+// multiples of 64, lda, za and ldh multiples of 8, A, H and bias 16-byte
+// aligned.  The bits of launch_gemm_bf16's products.
+struct LayerArgs {
+    const bf16_t *A;
+    int64_t lda, za;
+    const bf16_t *W;
+    const float *bias;
+    int64_t M;
+    int N, K, groups;
+    bf16_t *H;
+    int64_t ldh;
+};
+// whether the kernel is the better choice for M rows
+bool layer_forward_supported(int64_t M, int N, int K, int groups);
+hipError_t launch_layer_forward(const LayerArgs &a, hipStream_t s);
+
 // Fused inference forward pass: out = W4 h3 + b4 with h_l = GELU(W_l h_(l-1) + b_l),
 // h_0 = the 64-wide input rows.  W[l] holds the [out_l][in_l] BF16 weights in
 // fragment order (launch_swizzle_frag; in_l of layer 0 is 64), b[l] FP32.

@@ -168,6 +168,142 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(TM == 
 }
 
 // ---------------------------------------------------------------------------
+// Forward layer of a wide network: 128 rows x 256 units per 256-thread block,
+// four waves side by side, each 128 x 64 = 8 x 4 MFMA 16x16x32 tiles, two blocks
+// per CU so that one block's GELUs run beside the other's products.  The
+// activations pass through LDS (64 of the contraction at a time, two stages:
+// the next one is fetched into registers during the products and stored
+// behind them, one barrier per stage); the weights come in fragment order
+// straight from L2 into operand registers.  The outputs go through LDS once
+// more, so that every store writes whole lines.
+// What bounds it: of the per-species networks' layers the first (contraction
+// 64) its 1.9 GB of activations written, the second and third the matrix
+// cores and the GELUs: 65,536 rows of nine 1600-800-400 networks 0.68 + 1.99 +
+// 0.66 ms (790 TFLOP/s in the second), the served step 7.42 -> 3.49 ms.  The
+// 128 x 128 tile before, with both operands through one LDS stage and two
+// barriers per step, waited on its staging; 256 rows per block in eight
+// waves, which halve the weights' L2 traffic, took 0.80 + 2.05 + 0.73 ms; 8-byte
+// stores from the accumulators 1.30 + 2.44 + 0.92 ms.
+// Tiles of one row block run on one die (blocks go to the eight dies in turn),
+// so that its activations are fetched into one L2.
+// Same MFMA sequence per output element as gemm_bf16_kernel: the same bits.
+// ---------------------------------------------------------------------------
+constexpr int kLayerM = 128, kLayerN = 256, kLayerK = 64;
+
+__global__ void __launch_bounds__(256, 2) layer_forward_kernel(LayerArgs a)
+{
+    constexpr int RW = kLayerK + kPad;
+    __shared__ __attribute__((aligned(16))) bf16_t As[2][kLayerM][RW];
+    const int tn = (a.N + kLayerN - 1) / kLayerN, tm = (int)((a.M + kLayerM - 1) / kLayerM);
+    const int64_t total = (int64_t)tn * tm * a.groups, per = (total + 7) / 8;
+    const int64_t t = (int64_t)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((blockIdx.x >> 3) >= per || t >= total) return;
+    const int n0 = (int)(t % tn) * kLayerN, z = (int)(t / tn / tm);
+    const int64_t m0 = (t / tn % tm) * kLayerM;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wn = n0 + w * 64;
+    const bool on = wn < a.N;   // N is a multiple of 64: a wave's units are all inside or all past the layer
+    const bf16_t *A = a.A + (int64_t)z * a.za;
+    const bf16_t *W = a.W + (int64_t)z * a.N * a.K;
+    const int ksteps = a.K >> 5;
+    // staging: four rows' chunks per thread
+    const int sr = threadIdx.x >> 3, sk = (threadIdx.x & 7) * 8;
+    const bf16_t *src[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int64_t r = m0 + sr + 32 * i;
+        src[i] = A + (r < a.M ? r : a.M - 1) * a.lda + sk;
+    }
+    uint4 st0, st1, st2, st3;   // (as an array they would be kept in memory)
+    auto fetch = [&](int k0) __attribute__((always_inline)) {
+        st0 = *(const uint4 *)(src[0] + k0);
+        st1 = *(const uint4 *)(src[1] + k0);
+        st2 = *(const uint4 *)(src[2] + k0);
+        st3 = *(const uint4 *)(src[3] + k0);
+    };
+    auto stage = [&](int b) __attribute__((always_inline)) {
+        *(uint4 *)&As[b][sr][sk] = st0;
+        *(uint4 *)&As[b][sr + 32][sk] = st1;
+        *(uint4 *)&As[b][sr + 64][sk] = st2;
+        *(uint4 *)&As[b][sr + 96][sk] = st3;
+    };
+    const bf16_t *wf[4];
+    bf16x8 bq[2][4];   // weight fragments of two steps
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        wf[j] = W + ((int64_t)((on ? wn : 0) / 16 + j) * ksteps) * 512 + lane * 8;
+#pragma unroll
+        for (int d = 0; d < 2; d++) __builtin_memcpy(&bq[d][j], wf[j] + d * 512, 16);
+    }
+    floatx4 acc[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; i++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    stage(0);
+    __syncthreads();
+    int b = 0;
+    for (int k0 = 0; k0 < a.K; k0 += kLayerK, b ^= 1) {
+        const bool more = k0 + kLayerK < a.K;
+        if (more) fetch(k0 + kLayerK);
+        if (on) {
+#pragma unroll
+            for (int d = 0; d < 2; d++) {
+                // transposed tiles (weights first): a lane's four results are
+                // adjacent units of one row
+#pragma unroll
+                for (int i = 0; i < 8; i++) {
+                    bf16x8 x;
+                    __builtin_memcpy(&x, &As[b][i * 16 + (lane & 15)][32 * d + (lane >> 4) * 8], 16);
+#pragma unroll
+                    for (int j = 0; j < 4; j++)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bq[d][j], x, acc[i][j], 0, 0, 0);
+                }
+                const int kn = (k0 >> 5) + d + 2 < ksteps ? (k0 >> 5) + d + 2 : ksteps - 1;
+#pragma unroll
+                for (int j = 0; j < 4; j++) __builtin_memcpy(&bq[d][j], wf[j] + kn * 512, 16);
+            }
+        }
+        if (more) stage(b ^ 1);
+        __syncthreads();
+    }
+    if (!on) return;
+    bf16_t *H = a.H + (int64_t)z * a.N + wn;
+    const float *bias = a.bias + (int64_t)z * a.N + wn;
+    // the wave's 64 units of 16 rows at a time through its own piece of LDS
+    // (free after the last barrier), so that every store writes whole lines
+    bf16_t(*out)[RW] = &As[0][w * 16];
+    float4 bn[4];
+#pragma unroll
+    for (int j = 0; j < 4; j++) bn[j] = *(const float4 *)(bias + j * 16 + (lane >> 4) * 4);
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const bf16_t h[4] = {act_bf16(gelu(acc[i][j][0] + bn[j].x)), act_bf16(gelu(acc[i][j][1] + bn[j].y)),
+                                 act_bf16(gelu(acc[i][j][2] + bn[j].z)), act_bf16(gelu(acc[i][j][3] + bn[j].w))};
+            uint2 pk;
+            __builtin_memcpy(&pk, h, 8);
+            *(uint2 *)&out[lane & 15][j * 16 + (lane >> 4) * 4] = pk;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int h = 0; h < 2; h++) {
+            const int r = (lane >> 3) + 8 * h, c = (lane & 7) * 8;
+            const uint4 v = *(const uint4 *)&out[r][c];
+            const int64_t m = m0 + i * 16 + r;
+            if (m < a.M) *(uint4 *)(H + m * a.ldh + c) = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Fused forward pass (inference): 32 rows per block, four waves, 50 KB of
 // LDS, so that three blocks share a CU and one block's GELU epilogues overlap
 // another's matrix products; each layer is a 32 x N x K product with A (the
@@ -797,6 +933,26 @@ hipError_t launch_gemm_bf16(const GemmArgs &g, hipStream_t s)
         dim3 grid((unsigned)((g.N + kBN - 1) / kBN), (unsigned)((g.M + kBM - 1) / kBM), gz);
         hipLaunchKernelGGL(gemm_bf16_kernel<64>, grid, dim3(256), 0, s, g);
     }
+    return hipGetLastError();
+}
+
+static int64_t layer_tiles(int64_t M, int N, int groups)
+{
+    return (M + kLayerM - 1) / kLayerM * ((N + kLayerN - 1) / kLayerN) * groups;
+}
+
+// From 64 tiles on: 1,000 rows of the nine networks (8 row blocks; 456, 288 and
+// 144 tiles) 359 -> 272 us, 200 rows (114, 72 and 36 tiles, the last by the
+// general product) 258 -> 248; with fewer the 64 x 64 tiles have more blocks.
+bool layer_forward_supported(int64_t M, int N, int K, int groups)
+{
+    return N % 64 == 0 && K % kLayerK == 0 && layer_tiles(M, N, groups) >= 64;
+}
+
+hipError_t launch_layer_forward(const LayerArgs &a, hipStream_t s)
+{
+    const int64_t tiles = layer_tiles(a.M, a.N, a.groups);
+    hipLaunchKernelGGL(layer_forward_kernel, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

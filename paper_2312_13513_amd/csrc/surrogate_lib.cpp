@@ -208,19 +208,26 @@ bool fused_ok(const chem_surr_s *s)
 int group_n(const chem_surr_s *s, int l) { return s->G == 1 || l == 0 ? s->out_l[l] : (l == 3 ? 1 : s->hg[l]); }
 bool grouped(const chem_surr_s *s, int l) { return s->G > 1 && l > 0; }
 
+// The fragment-order copy of the weights, made when they changed.
+hipError_t ensure_frag(chem_surr_s *s, hipStream_t st)
+{
+    if (s->frag_valid) return hipSuccess;
+    for (int l = 0; l < 4; l++) {
+        hipError_t e = chem::launch_swizzle_frag(s->wbf + s->off_W[l], s->out_l[l], s->in_l[l],
+                                                 s->wfrag + s->off_W[l], st);
+        if (e != hipSuccess) return e;
+    }
+    s->frag_valid = true;
+    return hipSuccess;
+}
+
 // Inference forward pass of all four layers in one kernel (activations in
-// LDS); the fragment-order copy of the weights is made when they changed.
+// LDS).
 hipError_t forward_fused(chem_surr_s *s, const bf16_t *X, int64_t rows, float *OUT, int64_t ldo,
                          hipStream_t st)
 {
-    if (!s->frag_valid) {
-        for (int l = 0; l < 4; l++) {
-            hipError_t e = chem::launch_swizzle_frag(s->wbf + s->off_W[l], s->out_l[l], s->in_l[l],
-                                                     s->wfrag + s->off_W[l], st);
-            if (e != hipSuccess) return e;
-        }
-        s->frag_valid = true;
-    }
+    hipError_t e = ensure_frag(s, st);
+    if (e != hipSuccess) return e;
     chem::MlpArgs a{};
     a.X = X;
     a.rows = rows;
@@ -251,7 +258,16 @@ hipError_t forward(chem_surr_s *s, const bf16_t *X, int rows, bf16_t *const H[3]
         float *outf = last ? OUT : U[l];
         const int64_t ldf = last ? ldo : N;
         bf16_t *outh = last ? nullptr : H[l];
-        if (!grouped(s, l)) {
+        const int groups = grouped(s, l) ? s->G : 1;
+        if (!last && !outf && ((uintptr_t)in | (uintptr_t)outh) % 16 == 0 &&
+            chem::layer_forward_supported(rows, N / groups, Kd, groups)) {
+            e = ensure_frag(s, st);
+            if (e == hipSuccess)
+                e = chem::launch_layer_forward(chem::LayerArgs{in, ld_in, Kd, s->wfrag + s->off_W[l],
+                                                               s->master + s->off_b[l], rows, N / groups, Kd, groups,
+                                                               outh, N},
+                                               st);
+        } else if (!grouped(s, l)) {
             e = gemm(in, ld_in, 1, s->wbf + s->off_W[l], Kd, 1, rows, N, Kd, epi, s->master + s->off_b[l], outf,
                      ldf, outh, N, nullptr, 0, st);
         } else {
