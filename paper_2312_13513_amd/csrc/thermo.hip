@@ -3,15 +3,16 @@
 // polynomials; Section 3.2: these kernels are compute-bound, keep their
 // coefficients in constant memory, and are split into segments to bound
 // register use; Section 2: the transport model is Cantera's mixture-averaged
-// one).  One thread per cell, cells in index order (SoA, coalesced).
+// one).  One thread per cell, cells in index order (SoA, coalesced); the transport
+// of mechanisms beyond 16 species has kernels of its own, 16 cells per wave
+// (transport_group_kernel).
 //
-// The coefficients are uniform across a wave, so every table read is a
-// scalar load through the scalar cache (the counterpart of CUDA's constant
-// memory); a cell's mole fractions and per-species reciprocals live in
-// registers, sized by a compile-time bound KM >= K.  The loops over the
-// second species index are unrolled over KM (guards against K are uniform
-// branches); the loops over the first index run at run time, except for
-// small KM where everything unrolls.  Costs per cell with K species:
+// In the kernels with one thread per cell the coefficients are uniform across a
+// wave, so every table read is a scalar load through the scalar cache (the
+// counterpart of CUDA's constant memory); a cell's mole fractions and
+// per-species reciprocals live in registers, sized by a compile-time bound
+// KM >= K, and every species loop is unrolled over KM (guards against K are
+// uniform branches).  Costs per cell with K species:
 //   viscosity (Wilke)       K^2 pair terms of 3 fused multiply-adds
 //   conductivity (Mathur)   K terms
 //   diffusion               K (K - 1) / 2 pair polynomials and reciprocals
@@ -54,7 +55,6 @@ struct TrView {
     const double *A;     // ld x ld at [k ld + j]: c2_kj (padding 0)
     const double *Bw;    // ld x ld: 2 c1_kj c2_kj
     const double *C;     // ld x ld: c1_kj^2 c2_kj
-    const double *c1;    // ld x ld: c1_kj (the factored form of the larger kernels)
     const double *B;     // ld x ld x 5: diffusion fits, D_jk = T^(3/2) B_jk(ln T) / p (symmetric; padding B = 1)
     const double *invW;  // ld (padding 1)
 };
@@ -63,7 +63,8 @@ struct TrView {
 // by Newton steps, e -> e^2.  Two steps give the correctly rounded 1/x (all
 // of 2^20 seeded x in [1e-12, 1e12] on gfx950); one step leaves about 10
 // ulp (2.2e-15), used for the per-species and per-pair factors of the
-// transport sums, where nothing cancels.
+// transport sums, where nothing cancels (in the group kernels for the pairs
+// alone: there the second step of the per-species ones is 2 % of the time).
 __device__ __forceinline__ double rcp_t(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
@@ -103,19 +104,6 @@ __device__ __forceinline__ double poly5(const double *c, const LnPow &p)
     return q + c[0];
 }
 
-// Call f(k) for k = 0 .. K-1: unrolled over KM when UO, else a run-time loop.
-template <int KM, bool UO, class F>
-__device__ __forceinline__ void for_species(int K, F &&f)
-{
-    if constexpr (UO) {
-#pragma unroll
-        for (int k = 0; k < KM; k++)
-            if (k < K) f(k);
-    } else {
-        for (int k = 0; k < K; k++) f(k);
-    }
-}
-
 // A cell's K mass fractions into registers, rows beyond K zero.  The loads
 // are unconditional (rows past K - 1 read row K - 1 again), so all of them
 // are in flight together; guarded loads would each wait for the last.
@@ -143,11 +131,8 @@ __device__ __forceinline__ void load_yr(const double *__restrict__ Y, int64_t ld
 }
 
 // MODE bit 1: viscosity and conductivity; bit 2: diffusion coefficients.
-// With UO every species loop unrolls and a cell's values stay in
-// registers; otherwise the outer loops run at run time and take X_k, y_k and
-// s_k again from the inputs (a run-time index cannot address registers).
-// UO is chosen per phase (see launch_transport).
-template <int KM, bool UO, int MODE, bool EX = false>
+// Every species loop unrolls and a cell's values stay in registers.
+template <int KM, int MODE, bool EX = false>
 __global__ void __launch_bounds__(kThermoBlock) transport_kernel(TrView v, const double *__restrict__ T,
                                                                  const double *__restrict__ p,
                                                                  const double *__restrict__ Y, int64_t ldY,
@@ -163,9 +148,8 @@ __global__ void __launch_bounds__(kThermoBlock) transport_kernel(TrView v, const
     const double sT = sqrt(Tc);
 
     // composition: y_k = max(Y_k, 0) / sum, X_k = (y_k / W_k) / sum_j (y_j / W_j);
-    // X_j = 0 for the padding rows j >= K, so the padded tables need no
-    // guards in the loops over j
-    double X[KM], yv[UO ? KM : 1];
+    // X_j = 0 for the padding rows j >= K
+    double X[KM], yv[KM];
     load_rows<KM>(Y, ldY, i, K, X);
     double ysum = 0.0;
 #pragma unroll
@@ -177,108 +161,296 @@ __global__ void __launch_bounds__(kThermoBlock) transport_kernel(TrView v, const
     double csum = 0.0;
 #pragma unroll
     for (int k = 0; k < KM; k++) {
-        if constexpr (UO) yv[k] = X[k] * inv_y;
+        yv[k] = X[k] * inv_y;
         X[k] = X[k] * inv_y * v.invW[k];
         csum += X[k];
     }
     const double inv_c = rcp_t(csum);
 #pragma unroll
     for (int k = 0; k < KM; k++) X[k] *= inv_c;
-    auto x_of = [&](int k) -> double {
-        if constexpr (UO) return X[k];
-        else return fmax(Y[(int64_t)k * ldY + i], 0.0) * inv_y * v.invW[k] * inv_c;
-    };
-    auto y_of = [&](int k) -> double {
-        if constexpr (UO) return yv[k];
-        else return fmax(Y[(int64_t)k * ldY + i], 0.0) * inv_y;
-    };
     const int ld = KM;
 
     if constexpr (MODE & 1) {
-        // up to 36 species: the expanded form on X, X/s, X/s^2; beyond, the
-        // factored form on X and 1/s (two vectors fewer in registers)
-        constexpr bool kExpand = KM <= 36;
         const double qT = sqrt(sT);
-        double V[KM], Wv[kExpand ? KM : 1];   // X_j / s_j and X_j / s_j^2, or 1 / s_j
+        double V[KM], Wv[KM];   // X_j / s_j and X_j / s_j^2
         double a1 = 0.0, a2 = 0.0;
 #pragma unroll
         for (int k = 0; k < KM; k++) {
             const double r = rcp_1(qT * fabs(poly5(v.P + kPoly * k, lnT)));
-            if constexpr (kExpand) {
-                V[k] = X[k] * r;
-                Wv[k] = V[k] * r;
-            } else {
-                V[k] = r;
-            }
+            V[k] = X[k] * r;
+            Wv[k] = V[k] * r;
             const double lk = sT * poly5(v.Q + kPoly * k, lnT);
             a1 = fma(X[k], lk, a1);
             a2 = fma(X[k], rcp_1(lk), a2);
         }
         lam[i] = 0.5 * (a1 + rcp_t(a2));
         double m = 0.0;
-        for_species<KM, UO>(K, [&](int k) {
-            const double sk = qT * fabs(poly5(v.P + kPoly * k, lnT));
-            const double *A = v.A + (int64_t)k * ld, *Bw = v.Bw + (int64_t)k * ld, *C = v.C + (int64_t)k * ld;
-            double den;
-            if constexpr (kExpand) {
+#pragma unroll
+        for (int k = 0; k < KM; k++)
+            if (k < K) {
+                const double sk = qT * fabs(poly5(v.P + kPoly * k, lnT));
+                const double *A = v.A + (int64_t)k * ld, *Bw = v.Bw + (int64_t)k * ld, *C = v.C + (int64_t)k * ld;
                 double d0 = 0.0, d1 = 0.0, d2 = 0.0;
 #pragma unroll
                 for (int j = 0; j < KM; j++)
-                    if (!UO || j < K) {   // unrolled kernels skip the padding, the others run through it
+                    if (j < K) {   // skips the padding
                         d0 = fma(A[j], X[j], d0);
                         d1 = fma(Bw[j], V[j], d1);
                         d2 = fma(C[j], Wv[j], d2);
                     }
-                den = fma(sk, fma(sk, d2, d1), d0);
-            } else {
-                // (1 + s_k c1_kj / s_j)^2 c2_kj X_j
-                const double *c1 = v.c1 + (int64_t)k * ld;
-                den = 0.0;
-#pragma unroll
-                for (int j = 0; j < KM; j++) {
-                    const double t = fma(sk * c1[j], V[j], 1.0);
-                    den = fma(X[j], t * t * A[j], den);
-                }
+                const double den = fma(sk, fma(sk, d2, d1), d0);
+                m = fma(X[k] * sk * sk, rcp_1(den), m);
             }
-            m = fma(x_of(k) * sk * sk, rcp_1(den), m);
-        });
         mu[i] = m;
     }
 
     if constexpr (MODE & 2) {
         const double t32_p = Tc * sT * rcp_1(p[i]);
-        if constexpr (UO) {
-            // S_k = sum_{j != k} X_j / B_jk(ln T); pairs j < k once each
-            double S[KM];
+        // S_k = sum_{j != k} X_j / B_jk(ln T); pairs j < k once each
+        double S[KM];
 #pragma unroll
-            for (int k = 0; k < KM; k++) S[k] = 0.0;
+        for (int k = 0; k < KM; k++) S[k] = 0.0;
 #pragma unroll
-            for (int k = 0; k < KM; k++)
-                if (k < K) {
-                    const double *B = v.B + (int64_t)k * ld * kPoly;
-#pragma unroll
-                    for (int j = k + 1; j < KM; j++)
-                        if (j < K) {
-                            const double ib = rcp_1(poly5(B + kPoly * j, lnT));
-                            S[j] = fma(X[k], ib, S[j]);
-                            S[k] = fma(X[j], ib, S[k]);
-                        }
-                    const double sk = S[k];
-                    D[(int64_t)k * ldD + i] = sk > 0.0 ? (1.0 - yv[k]) * t32_p * rcp_1(sk)
-                                                       : t32_p * poly5(B + kPoly * k, lnT);
-                }
-        } else {
-            // a run-time k cannot address the accumulators of the pairs
-            // (j < k, k): every species sums its own row (each pair twice)
-            for (int k = 0; k < K; k++) {
+        for (int k = 0; k < KM; k++)
+            if (k < K) {
                 const double *B = v.B + (int64_t)k * ld * kPoly;
-                double s = 0.0;
 #pragma unroll
-                for (int j = 0; j < KM; j++) {
-                    const double ib = rcp_1(poly5(B + kPoly * j, lnT));
-                    s = fma(j == k ? 0.0 : X[j], ib, s);
+                for (int j = k + 1; j < KM; j++)
+                    if (j < K) {
+                        const double ib = rcp_1(poly5(B + kPoly * j, lnT));
+                        S[j] = fma(X[k], ib, S[j]);
+                        S[k] = fma(X[j], ib, S[k]);
+                    }
+                const double sk = S[k];
+                D[(int64_t)k * ldD + i] = sk > 0.0 ? (1.0 - yv[k]) * t32_p * rcp_1(sk)
+                                                   : t32_p * poly5(B + kPoly * k, lnT);
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Transport of the larger mechanisms: 16 cells per wave, species in groups of four.
+// Lane 16 q + c holds cell c and, of every group g, species 4 g + q: the
+// operand and result layout of the FP64 matrix instructions
+//   16x16x4: D row 4 r + q in result r of lane (q, c), B row q in lane (q, c)
+//   4x4x4:   D row q, B row q in lane (q, c)
+// so the three contractions of the model run on them without a lane exchange:
+//   fits          sum_c coef_c (ln T)^c        rows = species or pairs, K = 4, c = 0 as the initial value
+//   Wilke sums    sum_j c2_kj (X_j, X_j/s'_j, X_j/s'_j^2)    rows = k, K = the species
+//   with s'_k = s_k W_k^(-1/4): c1_kj s_k / s_j = s'_k / s'_j, one matrix for
+//   all three sums
+// and a wave's table reads are one LDS read per operand instead of a scalar
+// load per coefficient.  The binary fits are evaluated once per pair: for groups
+// G1 <= G2 one 16x16x4 gives the 16 pairs (4 G1 + q, 4 G2 + r), which enter the
+// lane's own sum (species 4 G1 + q, weight X of 4 G2 + r) and four partial sums
+// over q (species 4 G2 + r), reduced over the wave's quarters by lane swaps.
+// What bounds them: the FP64 issue rate, which matrix and vector instructions
+// share (64 multiply-adds per clock and CU either way; both together take the
+// sum of their times): 35 species, 500,003 cells about 11,000 cycles of it per
+// 16 cells, 300 us (920 before, one cell per lane with the coefficients as
+// scalar loads: 27 KB of them per wave for the binary fits alone, through a 16 KB
+// scalar cache, one wait after another); 20 species 131 us (164), 64 species
+// 820 us (3503); 500 cells 14 us (138) at 35 species.  Two waves per SIMD asked
+// for, so that results stay in vector registers (else they pass through the
+// accumulation registers, +7 %); four cost spills (326 us).
+
+// Tables of a mechanism of NG groups, in doubles: per group fits (P rows, P
+// constants, Q rows, Q constants), 1/W and W^(-1/4); the Wilke matrix by (g, G)
+// tiles of 4x4; the binary fits by (G1 <= G2) tiles of 16 rows.
+constexpr int kFitLen = 40, kHeadLen = kFitLen + 8, kPairLen = 80;
+__host__ __device__ constexpr int grp_head(int NG) { return kHeadLen * NG; }
+__host__ __device__ constexpr int grp_wilke(int NG) { return 16 * NG * NG; }
+__host__ __device__ constexpr int grp_pairs(int NG) { return kPairLen * (NG * (NG + 1) / 2); }
+
+typedef double dx4 __attribute__((ext_vector_type(4)));
+typedef unsigned ux2 __attribute__((ext_vector_type(2)));
+
+// Threads per block: the tables of 13 and more groups leave room for one block.
+constexpr int grp_block(int NG) { return NG > 12 ? 512 : 256; }
+
+struct DPair {
+    double a, b;
+};
+
+// Halves: {a's lanes 0-31, b's lanes 0-31} and {a's 32-63, b's 32-63}.
+__device__ __forceinline__ DPair swap_halves(double a, double b)
+{
+    const ux2 ua = __builtin_bit_cast(ux2, a), ub = __builtin_bit_cast(ux2, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
+    return {__builtin_bit_cast(double, ux2{lo[0], hi[0]}), __builtin_bit_cast(double, ux2{lo[1], hi[1]})};
+}
+
+// Quarters: {a0, b0, a2, b2} and {a1, b1, a3, b3}.
+__device__ __forceinline__ DPair swap_quarters(double a, double b)
+{
+    const ux2 ua = __builtin_bit_cast(ux2, a), ub = __builtin_bit_cast(ux2, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap(ua.x, ub.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(ua.y, ub.y, false, false);
+    return {__builtin_bit_cast(double, ux2{lo[0], hi[0]}), __builtin_bit_cast(double, ux2{lo[1], hi[1]})};
+}
+
+// Sum over the four quarters, in every lane.
+__device__ __forceinline__ double sum_quarters(double x)
+{
+    const DPair h = swap_halves(x, x);
+    const double s = h.a + h.b;
+    const DPair g = swap_quarters(s, s);
+    return g.a + g.b;
+}
+
+// MODE bit 1: viscosity and conductivity; bit 2: diffusion coefficients.
+template <int NG, int MODE>
+__global__ void __launch_bounds__(grp_block(NG), 2) transport_group_kernel(const double *__restrict__ table, int K,
+                                                                    const double *__restrict__ T,
+                                                                    const double *__restrict__ p,
+                                                                    const double *__restrict__ Y, int64_t ldY,
+                                                                    int64_t n, double *__restrict__ mu,
+                                                                    double *__restrict__ lam,
+                                                                    double *__restrict__ D, int64_t ldD)
+{
+    extern __shared__ __align__(16) double tab[];
+    constexpr int kBlock = grp_block(NG), kHead = grp_head(NG), kWilke = grp_wilke(NG), kPairs = grp_pairs(NG);
+    constexpr int kFirst = kHead + (MODE & 1 ? kWilke : 0);   // head and Wilke matrix are contiguous
+    for (int e = threadIdx.x; e < kFirst / 2; e += kBlock)
+        ((double2 *)tab)[e] = ((const double2 *)table)[e];
+    if constexpr (MODE & 2)
+        for (int e = threadIdx.x; e < kPairs / 2; e += kBlock)
+            ((double2 *)(tab + kFirst))[e] = ((const double2 *)(table + kHead + kWilke))[e];
+    __syncthreads();
+    const int ng = (K + 3) >> 2;
+    const int64_t tiles = (n + 15) >> 4;
+
+    for (int64_t t = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); t < tiles;
+         t += (int64_t)gridDim.x * (kBlock / 64)) {
+        // opaque: else the table reads, the same in every turn, move before
+        // the loop and fill the registers
+        int lane = threadIdx.x & 63;
+        asm("" : "+v"(lane));
+        const int c = lane & 15, q = lane >> 4;
+        const int a4 = q * 4 + (lane & 3);   // this lane's element of a 4x4 operand
+        const int64_t cell = t * 16 + c;
+        const bool live = cell < n;
+        const int64_t i = live ? cell : n - 1;   // the tail's idle lanes repeat the last cell
+        // composition: y_k = max(Y_k, 0) / sum, X_k = (y_k / W_k) / sum_j (y_j / W_j), zero beyond K
+        double X[NG];
+#pragma unroll
+        for (int g = 0; g < NG; g++) {
+            const int k = 4 * g + q;
+            X[g] = Y[(int64_t)(k < K ? k : K - 1) * ldY + i];
+        }
+        const double Tc = T[i];
+        double ysum = 0.0;
+#pragma unroll
+        for (int g = 0; g < NG; g++) {
+            X[g] = 4 * g + q < K ? fmax(X[g], 0.0) : 0.0;
+            ysum += X[g];
+        }
+        const double inv_y = rcp_t(sum_quarters(ysum));
+        double yv[MODE & 2 ? NG : 1], csum = 0.0;
+#pragma unroll
+        for (int g = 0; g < NG; g++) {
+            const double y = X[g] * inv_y;
+            if constexpr (MODE & 2) yv[g] = y;
+            X[g] = y * tab[kFitLen * NG + 4 * g + q];
+            csum += X[g];
+        }
+        const double inv_c = rcp_t(sum_quarters(csum));
+#pragma unroll
+        for (int g = 0; g < NG; g++) X[g] *= inv_c;
+
+        const double x = log(Tc), sT = sqrt(Tc), x2 = x * x;
+        const double xp = q == 0 ? x : q == 1 ? x2 : q == 2 ? x2 * x : x2 * x2;   // row q of the powers
+
+        if constexpr (MODE & 1) {
+            const double qT = sqrt(sT);
+            double V[NG], Wv[NG];   // X / s' and X / s'^2
+            double s[NG];
+            const double *w4 = tab + (kFitLen + 4) * NG + q;
+            double a1 = 0.0, a2 = 0.0;
+#pragma unroll
+            for (int g = 0; g < NG; g++) {
+                const double *f = tab + kFitLen * g;
+                s[g] = qT * fabs(__builtin_amdgcn_mfma_f64_4x4x4f64(f[a4], xp, f[16 + q], 0, 0, 0));
+                const double r = rcp_t(s[g] * w4[4 * g]);
+                V[g] = X[g] * r;
+                Wv[g] = V[g] * r;
+                const double lk = sT * __builtin_amdgcn_mfma_f64_4x4x4f64(f[20 + a4], xp, f[36 + q], 0, 0, 0);
+                a1 = fma(X[g], lk, a1);
+                a2 = fma(X[g], rcp_t(lk), a2);
+            }
+            a1 = sum_quarters(a1);
+            a2 = sum_quarters(a2);
+            double m = 0.0;
+#pragma unroll
+            for (int g = 0; g < NG; g++) {
+                if (g >= ng) continue;
+                const double *w = tab + kHead + g * NG * 16 + a4;
+                double d0 = 0.0, d1 = 0.0, d2 = 0.0;
+#pragma unroll
+                for (int G = 0; G < NG; G++) {
+                    const double a = w[G * 16];
+                    d0 = __builtin_amdgcn_mfma_f64_4x4x4f64(a, X[G], d0, 0, 0, 0);
+                    d1 = __builtin_amdgcn_mfma_f64_4x4x4f64(a, V[G], d1, 0, 0, 0);
+                    d2 = __builtin_amdgcn_mfma_f64_4x4x4f64(a, Wv[G], d2, 0, 0, 0);
                 }
-                D[(int64_t)k * ldD + i] = s > 0.0 ? (1.0 - y_of(k)) * t32_p * rcp_1(s) : t32_p * poly5(B + kPoly * k, lnT);
+                // X_k mu_k / (d0 + 2 s' d1 + s'^2 d2); rows beyond K: X = 0 over a unit matrix row
+                const double sp = s[g] * w4[4 * g];
+                const double den = fma(sp, fma(sp, d2, 2.0 * d1), d0);
+                m = fma(X[g] * s[g] * s[g], rcp_t(den), m);
+            }
+            m = sum_quarters(m);
+            if (live && q == 0) {
+                lam[i] = 0.5 * (a1 + rcp_t(a2));
+                mu[i] = m;
+            }
+        }
+
+        if constexpr (MODE & 2) {
+            const double t32_p = Tc * sT * rcp_t(p[i]);
+            double S[NG];   // sum_{j != k} X_j / B_jk(ln T) of the lane's own species
+#pragma unroll
+            for (int g = 0; g < NG; g++) S[g] = 0.0;
+#pragma unroll
+            for (int G2 = 0; G2 < NG; G2++) {
+                if (G2 >= ng) continue;
+                // the group's four mole fractions in every lane
+                const DPair h = swap_halves(X[G2], X[G2]), x01 = swap_quarters(h.a, h.a),
+                            x23 = swap_quarters(h.b, h.b);
+                const double Xr[4] = {x01.a, x01.b, x23.a, x23.b};
+                double P[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int G1 = 0; G1 <= G2; G1++) {
+                    const double *b = tab + kFirst + (G2 * (G2 + 1) / 2 + G1) * kPairLen;
+                    const double2 c01 = *(const double2 *)(b + 64 + 4 * q), c23 = *(const double2 *)(b + 66 + 4 * q);
+                    dx4 v = {c01.x, c01.y, c23.x, c23.y};
+                    v = __builtin_amdgcn_mfma_f64_16x16x4f64(b[lane], xp, v, 0, 0, 0);
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        const double ib = rcp_1(v[r]);
+                        if (G1 < G2) {
+                            S[G1] = fma(Xr[r], ib, S[G1]);
+                            P[r] = fma(X[G1], ib, P[r]);
+                        } else {
+                            P[r] = fma(q == r ? 0.0 : X[G1], ib, P[r]);
+                        }
+                    }
+                }
+                // quarter q keeps the sum of species 4 G2 + q
+                const DPair p02 = swap_halves(P[0], P[2]), p13 = swap_halves(P[1], P[3]);
+                const DPair s4 = swap_quarters(p02.a + p02.b, p13.a + p13.b);
+                S[G2] += s4.a + s4.b;
+            }
+#pragma unroll
+            for (int g = 0; g < NG; g++) {
+                if (g >= ng) continue;
+                double d = (1.0 - yv[g]) * t32_p * rcp_t(S[g]);
+                if (!(S[g] > 0.0)) {   // a pure species: its own fit
+                    const double *b = tab + kFirst + (g * (g + 1) / 2 + g) * kPairLen;
+                    const double cf[kPoly] = {b[64 + 5 * q], b[5 * q], b[16 + 5 * q], b[32 + 5 * q], b[48 + 5 * q]};
+                    d = t32_p * poly5(cf, ln_powers(x));
+                }
+                if (live && 4 * g + q < K) D[(int64_t)(4 * g + q) * ldD + i] = d;
             }
         }
     }
@@ -414,78 +586,62 @@ __global__ void __launch_bounds__(kThermoBlock) t_from_h_kernel(const double *__
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + kThermoBlock - 1) / kThermoBlock); }
 
-// Dispatch on the smallest compile-time bound that holds K.  The bounds up to
-// 16 unroll every loop and run both phases in one kernel; 20 unrolls them in
-// two kernels (the size of the paper's CH4 mechanism); from 24 on the two
-// phases are separate kernels (the segments of Section 3.2: the fused
-// kernel's registers would cut occupancy to one or two waves per SIMD), the
-// diffusion phase unrolled at 24 (its triangular pair loop needs
-// compile-time indices) and both phases with run-time outer loops beyond.
+// Compile-time bounds of the species count: a call takes the smallest that
+// holds K.  The transport kernels with one cell per lane serve up to 16
+// species, the group kernels the rest, with their own list: 500,003 cells of 9
+// species 44 us by lanes and 72 by groups, 14 species 90 and 101, 20 species 164
+// and 131.  (Small calls are faster by groups at any count, 500 cells of 14
+// species 27 and 10 us, but a cell's bits do not depend on the call's size.)
 #define CHEM_TR_BOUNDS(X) X(9) X(12) X(16) X(20) X(24) X(36) X(48) X(64)
+#define CHEM_TR_LANE_BOUNDS(X) X(9) X(12) X(16)
+#define CHEM_TR_GROUPS(X) X(5) X(6) X(9) X(12) X(16)
+constexpr int kTrLaneMaxK = 16;
 
-// The kernel bound KM for K species (the tables' padded row count).
+// The cell-per-lane kernels' bound for K species (their tables' padded row count).
 int tr_bound(int K)
 {
 #define CHEM_TR_BOUND(KM) \
     if (K <= KM) return KM;
-    CHEM_TR_BOUNDS(CHEM_TR_BOUND)
+    CHEM_TR_LANE_BOUNDS(CHEM_TR_BOUND)
 #undef CHEM_TR_BOUND
     return -1;
 }
 
-// Doubles of the transport tables at bound L: P, Q, A, Bw, C, c1, B, invW.
-size_t tr_table_len(int L) { return 10 * (size_t)L + 4 * (size_t)L * L + 5 * (size_t)L * L + L; }
+// The group kernels' group count for K species.
+int tr_groups(int K)
+{
+#define CHEM_TR_GROUP(NG) \
+    if (K <= 4 * NG) return NG;
+    CHEM_TR_GROUPS(CHEM_TR_GROUP)
+#undef CHEM_TR_GROUP
+    return -1;
+}
+
+// Doubles of the cell-per-lane tables at bound L: P, Q, A, Bw, C, B, invW.
+size_t tr_table_len(int L) { return 10 * (size_t)L + 3 * (size_t)L * L + 5 * (size_t)L * L + L; }
 
 template <int KM>
 hipError_t launch_transport_km(const TrView &v, const double *T, const double *p, const double *Y, int64_t ldY,
                                int64_t n, double *mu, double *lam, double *D, int64_t ldD, hipStream_t st)
 {
     const dim3 g(blocks_for(n)), b(kThermoBlock);
-    if constexpr (KM <= 16) {
-        const bool ex = v.K == KM;
-#define CHEM_TR_UO(MODE)                                                                                      \
-    do {                                                                                                     \
-        if (ex)                                                                                              \
-            hipLaunchKernelGGL((transport_kernel<KM, true, MODE, true>), g, b, 0, st, v, T, p, Y, ldY, n, mu,  \
-                               lam, D, ldD);                                                                 \
-        else                                                                                                 \
-            hipLaunchKernelGGL((transport_kernel<KM, true, MODE, false>), g, b, 0, st, v, T, p, Y, ldY, n, mu, \
-                               lam, D, ldD);                                                                 \
+    const bool ex = v.K == KM;
+#define CHEM_TR_MODE(MODE)                                                                                     \
+    do {                                                                                                      \
+        if (ex)                                                                                               \
+            hipLaunchKernelGGL((transport_kernel<KM, MODE, true>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam,  \
+                               D, ldD);                                                                       \
+        else                                                                                                  \
+            hipLaunchKernelGGL((transport_kernel<KM, MODE, false>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam, \
+                               D, ldD);                                                                       \
     } while (0)
-        if (mu && D)
-            CHEM_TR_UO(3);
-        else if (mu)
-            CHEM_TR_UO(1);
-        else
-            CHEM_TR_UO(2);
-#undef CHEM_TR_UO
-    } else if constexpr (KM <= 20) {
-        // unrolled, in two kernels (the fused one would hold five species
-        // vectors: two waves per SIMD)
-        const bool ex = v.K == KM;
-        if (mu) {
-            if (ex)
-                hipLaunchKernelGGL((transport_kernel<KM, true, 1, true>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam,
-                                   D, ldD);
-            else
-                hipLaunchKernelGGL((transport_kernel<KM, true, 1, false>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam,
-                                   D, ldD);
-        }
-        if (D) {
-            if (ex)
-                hipLaunchKernelGGL((transport_kernel<KM, true, 2, true>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam,
-                                   D, ldD);
-            else
-                hipLaunchKernelGGL((transport_kernel<KM, true, 2, false>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam,
-                                   D, ldD);
-        }
-    } else {
-        if (mu)
-            hipLaunchKernelGGL((transport_kernel<KM, false, 1>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam, D, ldD);
-        if (D)
-            hipLaunchKernelGGL((transport_kernel<KM, KM <= 24, 2>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam, D,
-                               ldD);
-    }
+    if (mu && D)
+        CHEM_TR_MODE(3);
+    else if (mu)
+        CHEM_TR_MODE(1);
+    else
+        CHEM_TR_MODE(2);
+#undef CHEM_TR_MODE
     return hipGetLastError();
 }
 
@@ -494,9 +650,117 @@ hipError_t launch_transport(const TrView &v, const double *T, const double *p, c
 {
 #define CHEM_TR_CASE(KM) \
     if (v.ld == KM) return launch_transport_km<KM>(v, T, p, Y, ldY, n, mu, lam, D, ldD, st);
-    CHEM_TR_BOUNDS(CHEM_TR_CASE)
+    CHEM_TR_LANE_BOUNDS(CHEM_TR_CASE)
 #undef CHEM_TR_CASE
     return hipErrorInvalidValue;
+}
+
+template <int NG, int MODE>
+hipError_t launch_group_mode(const double *table, int K, const double *T, const double *p, const double *Y,
+                             int64_t ldY, int64_t n, double *mu, double *lam, double *D, int64_t ldD,
+                             hipStream_t st)
+{
+    constexpr int lds =
+        8 * (grp_head(NG) + (MODE & 1 ? grp_wilke(NG) : 0) + (MODE & 2 ? grp_pairs(NG) : 0));
+    if constexpr (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)transport_group_kernel<NG, MODE>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    // as many blocks as the chip holds, each over every grid-th piece
+    constexpr int kBlock = grp_block(NG), per_cu = std::min(160 * 1024 / lds, 4), kCells = kBlock / 64 * 16;
+    const int64_t blocks = std::min<int64_t>((n + kCells - 1) / kCells, 256 * per_cu);
+    hipLaunchKernelGGL((transport_group_kernel<NG, MODE>), dim3((unsigned)blocks), dim3(kBlock), lds, st, table,
+                       K, T, p, Y, ldY, n, mu, lam, D, ldD);
+    return hipGetLastError();
+}
+
+hipError_t launch_transport_groups(const double *table, int K, const double *T, const double *p, const double *Y,
+                                   int64_t ldY, int64_t n, double *mu, double *lam, double *D, int64_t ldD,
+                                   hipStream_t st)
+{
+    const int ng = tr_groups(K);
+#define CHEM_TR_CASE(NG)                                                                                        \
+    if (ng == NG)                                                                                               \
+        return mu && D ? launch_group_mode<NG, 3>(table, K, T, p, Y, ldY, n, mu, lam, D, ldD, st)               \
+               : mu    ? launch_group_mode<NG, 1>(table, K, T, p, Y, ldY, n, mu, lam, D, ldD, st)               \
+                       : launch_group_mode<NG, 2>(table, K, T, p, Y, ldY, n, mu, lam, D, ldD, st);
+    CHEM_TR_GROUPS(CHEM_TR_CASE)
+#undef CHEM_TR_CASE
+    return hipErrorInvalidValue;
+}
+
+// Host tables of the cell-per-lane kernels (diff: K x K x 5, symmetric).
+std::vector<double> lane_tables(int K, const std::vector<double> &W, const double *visc, const double *cond,
+                                const double *diff)
+{
+    const int L = tr_bound(K);
+    const size_t LL = (size_t)L * L;
+    std::vector<double> t(tr_table_len(L), 0.0);
+    double *P = t.data(), *Q = P + 5 * L, *A = Q + 5 * L, *Bw = A + LL, *C = Bw + LL, *B = C + LL;
+    double *iw = B + 5 * LL;
+    for (int k = 0; k < L; k++) {
+        P[5 * k] = Q[5 * k] = 1.0;   // padding rows: finite, and weighted by X = 0
+        iw[k] = 1.0;
+        for (int j = 0; j < L; j++) B[((size_t)k * L + j) * 5] = 1.0;
+    }
+    for (int k = 0; k < K; k++) {
+        for (int c = 0; c < 5; c++) {
+            P[5 * k + c] = visc[5 * k + c];
+            Q[5 * k + c] = cond[5 * k + c];
+        }
+        iw[k] = 1.0 / W[k];
+        for (int j = 0; j < K; j++) {
+            const double c1 = std::pow(W[j] / W[k], 0.25), c2 = 1.0 / std::sqrt(8.0 * (1.0 + W[k] / W[j]));
+            A[(size_t)k * L + j] = c2;
+            Bw[(size_t)k * L + j] = 2.0 * c1 * c2;
+            C[(size_t)k * L + j] = std::sqrt(W[j] / W[k]) * c2;
+            for (int c = 0; c < 5; c++) B[((size_t)k * L + j) * 5 + c] = diff[((size_t)k * K + j) * 5 + c];
+        }
+    }
+    return t;
+}
+
+// Host tables of the group kernels, in the lanes' operand orders.  Padding
+// species have the fit 1, weight 1 and a zero mole fraction.
+std::vector<double> group_tables(int K, const std::vector<double> &W, const double *visc, const double *cond,
+                                 const double *diff)
+{
+    const int NG = tr_groups(K);
+    std::vector<double> t((size_t)grp_head(NG) + grp_wilke(NG) + grp_pairs(NG), 0.0);
+    for (int g = 0; g < NG; g++)
+        for (int i = 0; i < 4; i++) {
+            const int k = 4 * g + i;
+            double *f = t.data() + kFitLen * g, *w = t.data() + kFitLen * NG;
+            for (int c = 0; c < 4; c++) {
+                f[c * 4 + i] = k < K ? visc[5 * k + c + 1] : 0.0;
+                f[20 + c * 4 + i] = k < K ? cond[5 * k + c + 1] : 0.0;
+            }
+            f[16 + i] = k < K ? visc[5 * k] : 1.0;
+            f[36 + i] = k < K ? cond[5 * k] : 1.0;
+            w[4 * g + i] = k < K ? 1.0 / W[k] : 1.0;
+            w[4 * NG + 4 * g + i] = k < K ? std::pow(W[k], -0.25) : 1.0;
+        }
+    double *M = t.data() + grp_head(NG);
+    for (int g = 0; g < NG; g++)
+        for (int G = 0; G < NG; G++)
+            for (int q = 0; q < 4; q++)
+                for (int i = 0; i < 4; i++) {
+                    const int k = 4 * g + i, j = 4 * G + q;
+                    M[(g * NG + G) * 16 + q * 4 + i] =
+                        k < K && j < K ? 1.0 / std::sqrt(8.0 * (1.0 + W[k] / W[j])) : 1.0;
+                }
+    double *b = M + grp_wilke(NG);
+    for (int G2 = 0; G2 < NG; G2++)
+        for (int G1 = 0; G1 <= G2; G1++, b += kPairLen)
+            for (int q = 0; q < 4; q++)
+                for (int r = 0; r < 4; r++) {
+                    const int j = 4 * G1 + q, k = 4 * G2 + r;
+                    const double *a = j < K && k < K ? diff + ((size_t)k * K + j) * 5 : nullptr;
+                    for (int c = 0; c < 4; c++) b[c * 16 + q + 4 * r] = a ? a[c + 1] : 0.0;
+                    b[64 + 4 * q + r] = a ? a[0] : 1.0;
+                }
+    return t;
 }
 
 hipError_t launch_h_cp(const DevMechView &m, const double *T, const double *Y, int64_t ldY, int64_t n, double *h,
@@ -563,40 +827,19 @@ int chem_set_transport(chem_mech m, const double *visc, const double *cond, cons
     const int K = m->host.K;
     if (K > chem::kTrMaxK)
         return fail(CHEM_EUNSUP, "the property kernels hold at most " + std::to_string(chem::kTrMaxK) + " species");
-    const int L = chem::tr_bound(K);
-    const size_t LL = (size_t)L * L;
-    std::vector<double> t(chem::tr_table_len(L), 0.0);
-    double *P = t.data(), *Q = P + 5 * L, *A = Q + 5 * L, *Bw = A + LL, *C = Bw + LL, *c1t = C + LL, *B = c1t + LL;
-    double *iw = B + 5 * LL;
-    for (int k = 0; k < L; k++) {
-        P[5 * k] = Q[5 * k] = 1.0;   // padding rows: finite, and weighted by X = 0
-        iw[k] = 1.0;
-        for (int j = 0; j < L; j++) B[((size_t)k * L + j) * 5] = 1.0;
-    }
+    for (int e = 0; e < 5 * K; e++)
+        if (!std::isfinite(visc[e]) || !std::isfinite(cond[e]))
+            return fail(CHEM_EINVAL, "transport fits must be finite");
     for (int k = 0; k < K; k++)
-        for (int c = 0; c < 5; c++) {
-            P[5 * k + c] = visc[5 * k + c];
-            Q[5 * k + c] = cond[5 * k + c];
-            if (!std::isfinite(P[5 * k + c]) || !std::isfinite(Q[5 * k + c]))
-                return fail(CHEM_EINVAL, "transport fits must be finite");
-        }
-    for (int k = 0; k < K; k++)
-        for (int j = 0; j < K; j++) {
-            const double Wk = m->W[k], Wj = m->W[j];
-            const double c1 = std::pow(Wj / Wk, 0.25), c2 = 1.0 / std::sqrt(8.0 * (1.0 + Wk / Wj));
-            A[(size_t)k * L + j] = c2;
-            Bw[(size_t)k * L + j] = 2.0 * c1 * c2;
-            C[(size_t)k * L + j] = std::sqrt(Wj / Wk) * c2;
-            c1t[(size_t)k * L + j] = c1;
+        for (int j = 0; j < K; j++)
             for (int c = 0; c < 5; c++) {
                 const double a = diff[((size_t)k * K + j) * 5 + c];
                 if (!std::isfinite(a)) return fail(CHEM_EINVAL, "transport fits must be finite");
                 if (a != diff[((size_t)j * K + k) * 5 + c])
                     return fail(CHEM_EINVAL, "the binary diffusion fits must be symmetric in the two species");
-                B[((size_t)k * L + j) * 5 + c] = a;
             }
-        }
-    for (int k = 0; k < K; k++) iw[k] = 1.0 / m->W[k];
+    const std::vector<double> t = K <= chem::kTrLaneMaxK ? chem::lane_tables(K, m->W, visc, cond, diff)
+                                                         : chem::group_tables(K, m->W, visc, cond, diff);
     int prev = 0;
     if (hipGetDevice(&prev) != hipSuccess) return fail(CHEM_EHIP, "hipGetDevice failed");
     int rc = check_hip(hipSetDevice(m->device), "hipSetDevice");
@@ -672,11 +915,15 @@ int chem_transport_field(chem_mech m, const double *T, const double *p, const do
     if (!is_device_ptr(T) || !is_device_ptr(Y) || (D && !is_device_ptr(p)) || !dev_or_null(mu) ||
         !dev_or_null(lam) || !dev_or_null(D))
         return fail(CHEM_EINVAL, "T, p, Y, mu, lam and D must be device pointers");
-    const int K = m->host.K, L = chem::tr_bound(K);
-    const size_t LL = (size_t)L * L;
+    const int K = m->host.K;
     const double *t = (const double *)m->transport_block;
+    if (K > chem::kTrLaneMaxK)
+        return check_hip(chem::launch_transport_groups(t, K, T, p, Y, ldY, n, mu, lam, D, ldD, (hipStream_t)stream),
+                         "transport launch");
+    const int L = chem::tr_bound(K);
+    const size_t LL = (size_t)L * L;
     chem::TrView v{K, L, t, t + 5 * L, t + 10 * L, t + 10 * L + LL, t + 10 * L + 2 * LL, t + 10 * L + 3 * LL,
-                   t + 10 * L + 4 * LL, t + 10 * L + 9 * LL};
+                   t + 10 * L + 8 * LL};
     return check_hip(chem::launch_transport(v, T, p, Y, ldY, n, mu, lam, D, ldD, (hipStream_t)stream),
                      "transport launch");
 }
