@@ -112,7 +112,7 @@ struct ApplyArgs {
     double elem_tol, sum_tol, neg_tol, T_out_min, T_out_max, T_in_min, T_in_max, dT_gate;
 };
 
-// Decode, temperature recovery and checks, one thread per cell: accepted
+// Decode, temperature recovery and checks (p is not read): accepted
 // cells take the prediction in place; rejected ones keep their state, get
 // mask[i] = 1 (if mask) and their index base + i appended to list (count in
 // *count).  status[i] (if status) is set to 0 for every cell.

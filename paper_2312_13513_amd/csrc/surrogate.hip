@@ -9,6 +9,9 @@
 // Adam; here its input is [T, p, BoxCox(Y)] and its output the z-scored
 // change of the mass fractions over one flow step.
 
+#include <algorithm>
+
+#include "quarters.h"
 #include "surrogate_math.h"
 
 namespace chem {
@@ -489,32 +492,48 @@ __global__ void __launch_bounds__(64 * kMlpWaves, 3) mlp_forward_kernel(MlpArgs 
 // below the BF16 rounding of the feature
 __device__ __forceinline__ double boxcox(double y) { return (exp2(0.1 * log2(fmax(y, 0.0))) - 1.0) / 0.1; }
 
+// 16 cells per wave, lane 16 q + c: cell c, features 4 g + q for g < NG (NG >= the
+// feature groups in use).  The rows are put together in LDS and leave as whole
+// lines.  Bound by the FP64 rate (an exponential, a logarithm and a division per
+// species): 2,097,152 cells of 35 species 0.43 ms (0.41 with a cell per thread and
+// 16-byte stores a row apart); 1,000 cells 9 us (25, all in one thread's chain).
+constexpr int kRowPad = 64;   // features of a row
+template <int NG>
 __global__ void __launch_bounds__(256) encode_kernel(const double *__restrict__ T,
                                                      const double *__restrict__ p,
                                                      const double *__restrict__ Y, int64_t ldY,
-                                                     int64_t n, int K, int nin_pad,
-                                                     const double *__restrict__ norm,
+                                                     int64_t n, int K, const double *__restrict__ norm,
                                                      bf16_t *__restrict__ X)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    __shared__ __align__(16) bf16_t rows[4][16][kRowPad + 8];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
+    const int64_t r0 = ((int64_t)blockIdx.x * 4 + w) * 16;
+    const int64_t i = r0 + c < n ? r0 + c : n - 1;
     const int nin = K + 2;
     const double *mu = norm, *sg = norm + nin;
-    bf16_t *row = X + i * nin_pad;
-    for (int j = 0; j < nin_pad; j += 8) {
-        uint4 pk;
-        bf16_t *v = (bf16_t *)&pk;
+    double raw[NG];
 #pragma unroll
-        for (int e = 0; e < 8; e++) {
-            const int f = j + e;
-            double z = 0.0;
+    for (int g = 0; g < NG; g++) {
+        const int f = 4 * g + q < nin ? 4 * g + q : nin - 1;
+        raw[g] = (f == 0 ? T : f == 1 ? p : Y + (int64_t)(f - 2) * ldY)[i];
+    }
+#pragma unroll
+    for (int g = 0; g < kRowPad / 4; g++) {
+        double z = 0.0;
+        if (g < NG) {
+            const int f = 4 * g + q;
             if (f < nin) {
-                const double raw = f == 0 ? T[i] : (f == 1 ? p[i] : boxcox(Y[(int64_t)(f - 2) * ldY + i]));
-                if (sg[f] >= 1e-12) z = (raw - mu[f]) / sg[f];
+                const double v = f < 2 ? raw[g < NG ? g : 0] : boxcox(raw[g < NG ? g : 0]);
+                if (sg[f] >= 1e-12) z = (v - mu[f]) / sg[f];
             }
-            v[e] = to_bf16((float)z);
         }
-        *(uint4 *)(row + j) = pk;
+        rows[w][c][4 * g + q] = to_bf16((float)z);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int r = (lane >> 3) + 8 * h, ch = (lane & 7) * 8;
+        if (r0 + r < n) *(uint4 *)(X + (r0 + r) * kRowPad + ch) = *(const uint4 *)&rows[w][r][ch];
     }
 }
 
@@ -590,175 +609,163 @@ __global__ void __launch_bounds__(256) fit_norm_kernel(const double *__restrict_
 // ---------------------------------------------------------------------------
 constexpr int kApplyMaxE = 8;   // elements the decode kernel handles
 
-// mass-specific enthalpy and cp of the mixture Y[0..K) (KM >= K, static loop)
-// Thermo of species k at T (the NASA range of the lane's T): cp/R and H/(R T).
-__device__ __forceinline__ void species_cp_hrt(const ApplyArgs &a, const double *species, int k, double T,
-                                               double invT, double &cp, double &hrt)
+// Decode, checks and temperature recovery: 16 cells per wave, lane 16 q + c: cell
+// c, species 4 g + q for g < NG; sums over the species are a lane's own part, then
+// over the quarters (the same bits in each).  The tables are in LDS, read by
+// lane: species k of the wave's quarters and, by each cell's T, range.
+// Temperature: Newton on h(T, Y) = h0 from T0, |dT| < 1e-10 K, at most 20 steps, T
+// kept in [200, 3500] K, on the mixture's polynomial coefficients (one pass over
+// the species, after which a step costs two quartics), rebuilt after a step that may
+// have crossed a range boundary.
+// Bound by the FP64 rate and near it by memory (1.5 GB): 2,097,152 cells of 35
+// species 0.50 ms (0.95 with a cell per thread and the sums over the species in every
+// step), 65,536 cells of 9 species 12 us (111), 1,000 cells of 35 species 10.5 us (33).
+template <int NG, int KE>
+__global__ void __launch_bounds__(256, NG <= 9 && KE <= 4 ? 4 : 3) apply_kernel(ApplyArgs a, double *__restrict__ T, double *__restrict__ Y,
+                                                    int64_t ldY, int64_t n, int64_t base,
+                                                    const float *__restrict__ out, int nout_pad,
+                                                    int32_t *__restrict__ mask, int32_t *__restrict__ status,
+                                                    int32_t *__restrict__ list, int64_t *__restrict__ count)
 {
-    const double *s = species + k * kSpeciesLen;
-    const bool low = !a.two_range || T < s[0];
-    double r[11];
-    const double *c = s + 1 + (low ? 0 : kRangeLen);
-#pragma unroll
-    for (int j = 0; j < 11; j++)
-        if (j != 6) r[j] = c[j];
-    cp = r[0] + T * (r[1] + T * (r[2] + T * (r[3] + T * r[4])));
-    hrt = r[0] + T * (r[7] + T * (r[8] + T * (r[9] + T * r[10]))) + r[5] * invT;
-}
-
-// Mixture enthalpy (J/kg) and cp (J/(kg K)) at T: sums over species in order,
-// each term Y_k (R/W_k) times T H_k/(R T), resp. cp_k/R.
-template <int KM>
-__device__ __forceinline__ void mix_h_cp(const ApplyArgs &a, const double *species, double T,
-                                         const double (&Y)[KM], double &hm, double &cm)
-{
-    double h = 0.0, c = 0.0;
-    const double invT = 1.0 / T;
-#pragma unroll
-    for (int k = 0; k < KM; k++) {
-        if (k < a.K) {
-            double cp, hrt;
-            species_cp_hrt(a, species, k, T, invT, cp, hrt);
-            const double yr = Y[k] * a.rw[k];
-            h += yr * (T * hrt);
-            c += yr * cp;
-        }
+    constexpr int KM = 4 * NG;
+    __shared__ double sp[KM * kSpeciesLen], rw[KM], mu[KM], sg[KM], nc[KE * KM];
+    const int K = a.K, E = a.E;
+    for (int j = threadIdx.x; j < K * kSpeciesLen; j += 256) sp[j] = a.species[j];
+    for (int j = threadIdx.x; j < K; j += 256) {
+        rw[j] = a.rw[j];
+        mu[j] = a.mu_y[j];
+        sg[j] = a.sig_y[j];
     }
-    hm = h;
-    cm = c;
-}
-
-// Decode, checks and temperature recovery, one thread per cell.  The input
-// state is read once: its element content, the element residual of the
-// prediction and the input enthalpy are accumulated in the same pass, so
-// only the predicted mass fractions stay in registers.  The block first
-// copies the species thermo blocks into LDS, where the enthalpy Newton
-// iterations read them.  With V4 (the output rows 16-byte aligned) a cell's
-// network outputs are read four at a time; one float per load touches a
-// different cache line in every lane of a wave for each species.
-template <int KM, int KE, bool V4>
-__global__ void __launch_bounds__(256, 3) apply_kernel(ApplyArgs a, double *__restrict__ T,
-                                                    const double *__restrict__ p,
-                                                    double *__restrict__ Y, int64_t ldY, int64_t n,
-                                                    int64_t base, const float *__restrict__ out,
-                                                    int nout_pad, int32_t *__restrict__ mask,
-                                                    int32_t *__restrict__ status,
-                                                    int32_t *__restrict__ list,
-                                                    int64_t *__restrict__ count)
-{
-    __shared__ double sp_lds[KM * kSpeciesLen];
-    for (int j = threadIdx.x; j < a.K * kSpeciesLen; j += 256) sp_lds[j] = a.species[j];
+    for (int j = threadIdx.x; j < KE * K; j += 256) nc[j / K * KM + j % K] = j < E * K ? a.ncoef[j] : 0.0;
+    const bool one = !a.two_range;
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool reject = false;
-    if (i < n) {
-        (void)p;
-        const int K = a.K;
+    const int64_t tiles = (n + 15) >> 4;
+    for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < tiles; t += (int64_t)gridDim.x * 4) {
+        // opaque: else table reads that are the same in every turn move before the loop
+        int lane = threadIdx.x & 63;
+        asm("" : "+v"(lane));
+        const int c = lane & 15, q = lane >> 4;
+        const bool live = t * 16 + c < n;
+        const int64_t i = live ? t * 16 + c : n - 1;   // the tail's idle lanes repeat the last cell
         const double T0 = T[i];
+        double y[NG];
+        float o[NG];
+#pragma unroll
+        for (int g = 0; g < NG; g++) {
+            const int k = 4 * g + q < K ? 4 * g + q : K - 1;
+            y[g] = Y[(int64_t)k * ldY + i];
+            o[g] = out[i * nout_pad + k];
+        }
         const double invT0 = 1.0 / T0;
-        double Y1[KM];
-        bool ok = true;
-        double sum = 0.0, ymin = 1e300, h0 = 0.0;
-        double res[KE], ref[KE];
+        double sum = 0.0, h0 = 0.0, res[KE], ref[KE], mlo = 1e300, mhi = -1e300;
+        bool bad = false;
 #pragma unroll
         for (int e = 0; e < KE; e++) res[e] = ref[e] = 0.0;
-        float4 o4 = make_float4(0.f, 0.f, 0.f, 0.f);   // outputs k .. k+3 (V4)
 #pragma unroll
-        for (int k = 0; k < KM; k++) {
-            Y1[k] = 0.0;
-            if (k < K) {
-                const double y0 = Y[(int64_t)k * ldY + i];
-                float o;   // the network's output for species k
-                if constexpr (V4) {
-                    // k + 3 < round_up(K, 4) <= nout_pad: inside the row
-                    if (k % 4 == 0) o4 = *(const float4 *)(out + i * nout_pad + k);
-                    o = (k % 4 == 0) ? o4.x : (k % 4 == 1) ? o4.y : (k % 4 == 2) ? o4.z : o4.w;
-                } else {
-                    o = out[i * nout_pad + k];
-                }
-                const double v = y0 + a.mu_y[k] + a.sig_y[k] * (double)o;
-                Y1[k] = v;
-                ok = ok && isfinite(v);
-                sum += v;
-                ymin = fmin(ymin, v);
+        for (int g = 0; g < NG; g++) {
+            const bool in = 4 * g + q < K;
+            const int k = in ? 4 * g + q : K - 1;
+            const double y0 = in ? y[g] : 0.0;
+            const double v = in ? y0 + mu[k] + sg[k] * (double)o[g] : 0.0;
+            y[g] = v;
+            bad = bad | !isfinite(v) | (v < -a.neg_tol);
+            sum += v;
 #pragma unroll
-                for (int e = 0; e < KE; e++)
-                    if (e < a.E) {
-                        const double nk = a.ncoef[e * K + k];
-                        res[e] += nk * (v - y0);
-                        ref[e] += nk * y0;
-                    }
-                double cp, hrt;
-                species_cp_hrt(a, sp_lds, k, T0, invT0, cp, hrt);
-                h0 += (y0 * a.rw[k]) * (T0 * hrt);
+            for (int e = 0; e < KE; e++) {
+                const double nk = nc[e * KM + k];
+                res[e] += nk * (v - y0);
+                ref[e] += nk * y0;
+                asm volatile("" : "+v"(res[e]), "+v"(ref[e]));
             }
+            const double *s = sp + k * kSpeciesLen;
+            const double *r = s + 1 + ((one | (T0 < s[0])) ? 0 : kRangeLen);
+            mlo = fmin(mlo, s[0]);
+            mhi = fmax(mhi, s[0]);
+            const double hrt = r[0] + T0 * (r[7] + T0 * (r[8] + T0 * (r[9] + T0 * r[10]))) + r[5] * invT0;
+            h0 += (y0 * rw[k]) * (T0 * hrt);
+            // the sums stay here: moved to their use, they would leave every coefficient in registers
+            asm volatile("" : "+v"(h0), "+v"(sum));
         }
+        // any of a cell's four lanes
+        unsigned long long bb = __ballot(bad);
+        bb |= bb >> 32;
+        bb |= bb >> 16;
+        bool ok = !((bb >> c) & 1);
+        sum = sum_quarters(sum);
+        h0 = sum_quarters(h0);
         // element residual relative to the element content of the input
 #pragma unroll
         for (int e = 0; e < KE; e++)
-            if (ok && e < a.E && fabs(res[e]) / fmax(ref[e], 1e-12) > a.elem_tol) ok = false;
-        if (ok && fabs(sum - 1.0) > a.sum_tol) ok = false;
-        if (ok && ymin < -a.neg_tol) ok = false;
-        double Tn = T0;
-        if (ok) {
-            double s2 = 0.0;
+            if (e < E && fabs(sum_quarters(res[e])) / fmax(sum_quarters(ref[e]), 1e-12) > a.elem_tol) ok = false;
+        if (fabs(sum - 1.0) > a.sum_tol) ok = false;
+        double s2 = 0.0;
 #pragma unroll
-            for (int k = 0; k < KM; k++) {
-                if (k < K) {
-                    Y1[k] = fmax(Y1[k], 0.0);
-                    s2 += Y1[k];
-                }
-            }
-            const double inv_s2 = 1.0 / s2;
-#pragma unroll
-            for (int k = 0; k < KM; k++)
-                if (k < K) Y1[k] = Y1[k] * inv_s2;
-            // Newton on h(T, Y2) = h0 from T0; |dT| < 1e-10 K, at most 20
-            // iterations, T kept in [200, 3500] K
-            bool conv = false;
-            double Tk = T0;
-            for (int it = 0; it < 20; it++) {
-                double hm, cm;
-                // an offset the compiler cannot see through keeps the table
-                // reads inside the loop: hoisted, the coefficients of every
-                // species would be held in registers across the iterations
-                int off = 0;
-                asm volatile("" : "+v"(off));
-                mix_h_cp<KM>(a, sp_lds + off, Tk, Y1, hm, cm);
-                const double dT = -(hm - h0) / cm;
-                Tk += dT;
-                Tk = fmin(fmax(Tk, 200.0), 3500.0);
-                if (fabs(dT) < 1e-10) {
-                    conv = true;
-                    break;
-                }
-            }
-            if (!conv || !(Tk >= a.T_out_min && Tk <= a.T_out_max)) ok = false;
-            if (ok && (T0 < a.T_in_min || T0 > a.T_in_max)) ok = false;
-            if (ok && a.dT_gate > 0.0 && fabs(Tk - T0) > a.dT_gate) ok = false;
-            Tn = Tk;
+        for (int g = 0; g < NG; g++) {
+            y[g] = fmax(y[g], 0.0);
+            s2 += y[g];
         }
-        if (ok) {
-            T[i] = Tn;
+        const double inv_s2 = 1.0 / sum_quarters(s2);
 #pragma unroll
-            for (int k = 0; k < KM; k++)
-                if (k < K) Y[(int64_t)k * ldY + i] = Y1[k];
+        for (int g = 0; g < NG; g++) y[g] *= inv_s2;
+        // every boundary lies in [mlo, mhi]: a step within one side of it keeps the ranges
+        mlo = min_quarters(mlo);
+        mhi = -min_quarters(-mhi);
+        bool conv = false, done = !ok, rebuild = true;
+        double Tk = T0, M[10];   // M: a1 .. a5 (cp), a2/2 .. a5/5 and a6 (h), R Y/W times
+        for (int it = 0; it < 20 && __any(!done); it++) {
+            if (__any(rebuild)) {
+                constexpr int src[10] = {0, 1, 2, 3, 4, 7, 8, 9, 10, 5};
+#pragma unroll
+                for (int j = 0; j < 10; j++) M[j] = 0.0;
+                int q2 = q;   // opaque, as lane
+                asm("" : "+v"(q2));
+#pragma unroll
+                for (int g = 0; g < NG; g++) {
+                    const int k = 4 * g + q2 < K ? 4 * g + q2 : K - 1;   // y = 0 beyond K
+                    const double *s = sp + k * kSpeciesLen;
+                    const double *r = s + 1 + ((one | (Tk < s[0])) ? 0 : kRangeLen);
+                    const double yr = y[g] * rw[k];
+#pragma unroll
+                    for (int j = 0; j < 10; j++) M[j] = fma(yr, r[src[j]], M[j]);
+                    asm volatile("" : "+v"(M[0]), "+v"(M[1]), "+v"(M[2]), "+v"(M[3]), "+v"(M[4]), "+v"(M[5]),
+                                 "+v"(M[6]), "+v"(M[7]), "+v"(M[8]), "+v"(M[9]));
+                }
+#pragma unroll
+                for (int j = 0; j < 10; j++) M[j] = sum_quarters(M[j]);
+            }
+            const double cm = fma(fma(fma(fma(M[4], Tk, M[3]), Tk, M[2]), Tk, M[1]), Tk, M[0]);
+            const double hm = fma(Tk, fma(fma(fma(fma(M[8], Tk, M[7]), Tk, M[6]), Tk, M[5]), Tk, M[0]), M[9]);
+            const double dT = -(hm - h0) / cm;
+            rebuild = false;
+            if (!done) {
+                const double Tn = fmin(fmax(Tk + dT, 200.0), 3500.0);
+                rebuild = a.two_range && !(Tk < mlo && Tn < mlo) && !(Tk >= mhi && Tn >= mhi);
+                Tk = Tn;
+                conv = done = fabs(dT) < 1e-10;
+            }
         }
-        if (mask) mask[i] = ok ? 0 : 1;
-        if (status) status[i] = 0;
-        reject = !ok;
-    }
-    // wave-aggregated append of the rejected cells
-    const unsigned long long bal = __ballot(reject);
-    if (bal) {
-        const int lane = threadIdx.x & 63;
-        const int leader = __ffsll((long long)bal) - 1;
-        unsigned long long slot = 0;
-        if (lane == leader) slot = atomicAdd((unsigned long long *)count, (unsigned long long)__popcll(bal));
-        slot = __shfl(slot, leader);
-        if (reject) {
-            const unsigned long long rank = __popcll(bal & ((1ull << lane) - 1ull));
-            list[slot + rank] = (int32_t)(base + i);
+        if (!conv || !(Tk >= a.T_out_min && Tk <= a.T_out_max)) ok = false;
+        if (T0 < a.T_in_min || T0 > a.T_in_max) ok = false;
+        if (a.dT_gate > 0.0 && fabs(Tk - T0) > a.dT_gate) ok = false;
+        if (live && ok) {
+            if (q == 0) T[i] = Tk;
+#pragma unroll
+            for (int g = 0; g < NG; g++)
+                if (4 * g + q < K) Y[(int64_t)(4 * g + q) * ldY + i] = y[g];
+        }
+        if (live && q == 0) {
+            if (mask) mask[i] = ok ? 0 : 1;
+            if (status) status[i] = 0;
+        }
+        // wave-aggregated append of the rejected cells
+        const bool reject = live && q == 0 && !ok;
+        const unsigned long long bal = __ballot(reject);
+        if (bal) {
+            const int leader = __ffsll((long long)bal) - 1;
+            unsigned long long slot = 0;
+            if (lane == leader) slot = atomicAdd((unsigned long long *)count, (unsigned long long)__popcll(bal));
+            slot = __shfl(slot, leader);
+            if (reject) list[slot + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)(base + i);
         }
     }
 }
@@ -1004,8 +1011,19 @@ hipError_t launch_encode(const double *T, const double *p, const double *Y, int6
                          int K, int nin_pad, const double *norm, bf16_t *X, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(encode_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, T, p, Y, ldY, n, K,
-                       nin_pad, norm, X);
+    if (nin_pad != kRowPad || K + 2 > kRowPad) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((n + 63) / 64));
+    // the feature groups of nine, 20 and 35 species, and the most a row holds
+#define CHEM_ENCODE(NG) hipLaunchKernelGGL((encode_kernel<NG>), grid, dim3(256), 0, s, T, p, Y, ldY, n, K, norm, X)
+    if (K + 2 <= 12)
+        CHEM_ENCODE(3);
+    else if (K + 2 <= 24)
+        CHEM_ENCODE(6);
+    else if (K + 2 <= 40)
+        CHEM_ENCODE(10);
+    else
+        CHEM_ENCODE(16);
+#undef CHEM_ENCODE
     return hipGetLastError();
 }
 
@@ -1035,36 +1053,31 @@ hipError_t launch_apply(const ApplyArgs &a, double *T, const double *p, double *
 {
     if (n <= 0) return hipSuccess;
     if (a.E > kApplyMaxE) return hipErrorInvalidValue;
-    const bool v4 = ((uintptr_t)out % 16 == 0) && nout_pad % 4 == 0;
-#define CHEM_APPLY_E(KM, KE)                                                                                  \
-    if (v4)                                                                                                   \
-        hipLaunchKernelGGL((apply_kernel<KM, KE, true>), dim3(blocks_for(n, 256)), dim3(256), 0, s, a, T, p, Y,  \
-                           ldY, n, base, out, nout_pad, mask, status, list, count);                           \
-    else                                                                                                      \
-        hipLaunchKernelGGL((apply_kernel<KM, KE, false>), dim3(blocks_for(n, 256)), dim3(256), 0, s, a, T, p, Y, \
-                           ldY, n, base, out, nout_pad, mask, status, list, count)
-#define CHEM_APPLY(KM)                                                                                        \
-    do {                                                                                                      \
-        if (a.E <= 4) {                                                                                       \
-            CHEM_APPLY_E(KM, 4);                                                                              \
-        } else {                                                                                              \
-            CHEM_APPLY_E(KM, kApplyMaxE);                                                                     \
-        }                                                                                                     \
+    (void)p;
+    // blocks of 64 cells, at most eight per CU: more go round, with the tables loaded once
+    const dim3 grid((unsigned)std::min<int64_t>((n + 63) / 64, 256 * 8));
+#define CHEM_APPLY(NG)                                                                                          \
+    do {                                                                                                        \
+        if (a.E <= 4)                                                                                           \
+            hipLaunchKernelGGL((apply_kernel<NG, 4>), grid, dim3(256), 0, s, a, T, Y, ldY, n, base, out,        \
+                               nout_pad, mask, status, list, count);                                            \
+        else                                                                                                    \
+            hipLaunchKernelGGL((apply_kernel<NG, kApplyMaxE>), grid, dim3(256), 0, s, a, T, Y, ldY, n, base,    \
+                               out, nout_pad, mask, status, list, count);                                       \
     } while (0)
-    if (a.K <= 16)
-        CHEM_APPLY(16);
-    else if (a.K <= 32)
-        CHEM_APPLY(32);
-    else if (a.K <= 40)
-        CHEM_APPLY(40);
+    if (a.K <= 12)
+        CHEM_APPLY(3);
+    else if (a.K <= 24)
+        CHEM_APPLY(6);
+    else if (a.K <= 36)
+        CHEM_APPLY(9);
     else if (a.K <= 48)
-        CHEM_APPLY(48);
+        CHEM_APPLY(12);
     else if (a.K <= kMaxSurrSpecies)
-        CHEM_APPLY(kMaxSurrSpecies);
+        CHEM_APPLY(16);
     else
         return hipErrorInvalidValue;
 #undef CHEM_APPLY
-#undef CHEM_APPLY_E
     return hipGetLastError();
 }
 

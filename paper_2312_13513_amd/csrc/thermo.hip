@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "host_common.h"
+#include "quarters.h"
 
 using chem_host::check_hip;
 using chem_host::fail;
@@ -263,41 +264,9 @@ __host__ __device__ constexpr int grp_wilke(int NG) { return 16 * NG * NG; }
 __host__ __device__ constexpr int grp_pairs(int NG) { return kPairLen * (NG * (NG + 1) / 2); }
 
 typedef double dx4 __attribute__((ext_vector_type(4)));
-typedef unsigned ux2 __attribute__((ext_vector_type(2)));
 
 // Threads per block: the tables of 13 and more groups leave room for one block.
 constexpr int grp_block(int NG) { return NG > 12 ? 512 : 256; }
-
-struct DPair {
-    double a, b;
-};
-
-// Halves: {a's lanes 0-31, b's lanes 0-31} and {a's 32-63, b's 32-63}.
-__device__ __forceinline__ DPair swap_halves(double a, double b)
-{
-    const ux2 ua = __builtin_bit_cast(ux2, a), ub = __builtin_bit_cast(ux2, b);
-    const auto lo = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
-    return {__builtin_bit_cast(double, ux2{lo[0], hi[0]}), __builtin_bit_cast(double, ux2{lo[1], hi[1]})};
-}
-
-// Quarters: {a0, b0, a2, b2} and {a1, b1, a3, b3}.
-__device__ __forceinline__ DPair swap_quarters(double a, double b)
-{
-    const ux2 ua = __builtin_bit_cast(ux2, a), ub = __builtin_bit_cast(ux2, b);
-    const auto lo = __builtin_amdgcn_permlane16_swap(ua.x, ub.x, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap(ua.y, ub.y, false, false);
-    return {__builtin_bit_cast(double, ux2{lo[0], hi[0]}), __builtin_bit_cast(double, ux2{lo[1], hi[1]})};
-}
-
-// Sum over the four quarters, in every lane.
-__device__ __forceinline__ double sum_quarters(double x)
-{
-    const DPair h = swap_halves(x, x);
-    const double s = h.a + h.b;
-    const DPair g = swap_quarters(s, s);
-    return g.a + g.b;
-}
 
 // MODE bit 1: viscosity and conductivity; bit 2: diffusion coefficients.
 template <int NG, int MODE>
