@@ -965,6 +965,9 @@ __global__ void __launch_bounds__(64) bdf_queue_kernel(Mech mech, double *__rest
 {
     __shared__ double nord[kLdsRows * (Mech::K + 1) * 64];
     const CellIO io = make_cell_io(T, p, Y, ldY, n, status, counters, prm);
+    // blocks beyond the queue's cells: their number may live on the device, under a
+    // grid made for all that could be there
+    if ((int64_t)blockIdx.x * 64 >= io.nq) return;
     run_lanes(mech, io, dt, queue, nord, sp);
 }
 

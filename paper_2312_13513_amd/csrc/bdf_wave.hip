@@ -1071,6 +1071,7 @@ bdf_wave_kernel(DevMechView m, Wave64Tables wt, double *__restrict__ T, const do
     __shared__ StepLds C;
     extern __shared__ double dyn[];
     const CellIO io = make_cell_io(T, p, Y, ldY, n, status, counters, prm);
+    if ((int64_t)blockIdx.x >= io.nq) return;   // fewer cells, counted on the device, than the grid
     if constexpr (QLDS) {
         WaveSys<NP, LT, RPL, true> S(m, wt, L, dyn);
         run_cells<WaveSys<NP, LT, RPL, true>, false>(S, C, io, dt, queue);
@@ -1095,6 +1096,7 @@ __global__ void __launch_bounds__(64) bdf_small_wave_kernel(DevMechView m, WaveT
     __shared__ StepLds C;
     extern __shared__ double dyn[];
     const CellIO io = make_cell_io(T, p, Y, ldY, n, status, counters, prm);
+    if ((int64_t)blockIdx.x >= io.nq) return;
     GroupSys<16, LT, 64> S(m, wt, L, dyn);
     run_cells<GroupSys<16, LT, 64>, false>(S, C, io, dt, queue);
 }
@@ -1137,6 +1139,7 @@ __global__ void __launch_bounds__(64) bdf_tile_kernel(DevMechView m, WaveTables 
     __shared__ WaveLds<NP, LT, 16> Ls[4];
     __shared__ StepLds Cs[4];
     extern __shared__ double dyn[];
+    if ((int64_t)blockIdx.x * 4 >= make_cell_io(T, p, Y, ldY, n, status, counters, prm).nq) return;
     if constexpr (STAGE) {
         const int tb = m.table_bytes;
         const int4 *src = (const int4 *)m.species;
