@@ -29,15 +29,17 @@ NO_MACHINE_LICM = ["-mllvm", "-disable-machine-licm"]
 
 
 # Merging the tails of the per-order code of the lane-group integrators turns
-# the Nordsieck columns into an array with a variable index, in memory.
+# the Nordsieck columns into an array with a variable index, in memory; in the
+# cell-per-lane integrators it merges stores to different state variables into one
+# through a chosen address (16 B of scratch, 1 % of small calls).
 NO_SINK = ["-mllvm", "-simplifycfg-sink-common=false"]
 
 
 def per_file_flags(src: str) -> list:
     name = os.path.basename(src)
-    if name.startswith("bdf_wave"):
+    if name.startswith("bdf_wave") or name.startswith("gen_"):
         return NO_MACHINE_LICM + NO_SINK
-    if name.startswith("gen_") or name == "chem_kernels.hip":
+    if name == "chem_kernels.hip":
         return NO_MACHINE_LICM
     return []
 

@@ -109,7 +109,9 @@ __device__ __forceinline__ bool lu_factor(double *M, unsigned long long &piv)
         ok = ok && (best != 0.0);
         if constexpr (k + 1 < N) {
             if (pk != k) {
-                static_for<0, N>([&](auto cc) {
+                // the multipliers left of the pivot stay where they are: the
+                // solve exchanges its right-hand side step by step
+                static_for<k, N>([&](auto cc) {
                     constexpr int c = decltype(cc)::value;
                     const double mk = reg_value(M[k * N + c]);
                     double nk = mk;
@@ -155,12 +157,9 @@ __device__ __forceinline__ void lu_solve(const double *M, unsigned long long piv
             b[r] = sw ? bk : br;
         });
         b[k] = nk;
-    });
-    static_for<1, N>([&](auto rc) {
-        constexpr int r = decltype(rc)::value;
-        static_for<0, r>([&](auto cc) {
-            constexpr int c = decltype(cc)::value;
-            b[r] -= M[r * N + c] * b[c];
+        static_for<k + 1, N>([&](auto rc) {
+            constexpr int r = decltype(rc)::value;
+            b[r] -= M[r * N + k] * b[k];
         });
     });
     static_for<0, N>([&](auto ri) {
@@ -280,25 +279,37 @@ struct LaneState {
     int nst, nfe, nje, nni, netf, ncfn;
 };
 
-// A component's columns 0 .. q pass through registers, zero beyond q: adding
-// them needs no guard, and each column is read and written once.
-template <int N>
-__device__ __forceinline__ void nord_predict(LaneState<N> &S)
+// A component's columns 0 .. JM (JM >= q) pass through registers, zero beyond q:
+// adding them needs no guard, and each column is read and written once.
+template <int JM, int N>
+__device__ __forceinline__ void nord_predict_to(LaneState<N> &S)
 {
 #pragma unroll
     for (int i = 0; i < N; i++) {
-        double v[kQmax + 1];
+        double v[JM + 1];
 #pragma unroll
-        for (int j = 0; j <= kQmax; j++) v[j] = S.z(j, i);
+        for (int j = 0; j <= JM; j++) v[j] = S.z(j, i);
 #pragma unroll
-        for (int j = 2; j <= kQmax; j++) v[j] = j <= S.q ? v[j] : 0.0;
+        for (int j = 2; j <= JM; j++) v[j] = j <= S.q ? v[j] : 0.0;
 #pragma unroll
-        for (int k = 1; k <= kQmax; k++)
+        for (int k = 1; k <= JM; k++)
 #pragma unroll
-            for (int j = kQmax; j >= k; j--) v[j - 1] += v[j];
+            for (int j = JM; j >= k; j--) v[j - 1] += v[j];
 #pragma unroll
-        for (int j = 0; j < kQmax; j++) S.z(j, i) = v[j];
+        for (int j = 0; j < JM; j++) S.z(j, i) = v[j];
     }
+}
+
+// Low orders in all lanes (a flame's many short integrations) have less to add.
+template <int N>
+__device__ __forceinline__ void nord_predict(LaneState<N> &S)
+{
+    if (__ballot(S.q > 1) == 0ull)
+        nord_predict_to<1>(S);
+    else if (__ballot(S.q > 2) == 0ull)
+        nord_predict_to<2>(S);
+    else
+        nord_predict_to<kQmax>(S);
 }
 
 template <int N>
@@ -816,9 +827,9 @@ __device__ void run_lanes(const Mech &mech, const CellIO &io, double t_end,
 
         // ---- bookkeeping: every path only says what is to be done, and each kind
         // of work below has one copy, which lanes of all paths run together.  (A
-        // wave alone on its CU is bound by fetching instructions: 9 species, 100 KB
+        // wave alone on its CU is bound by fetching instructions: 9 species, 97 KB
         // of code against 150 KB with the copies inlined in every path, of which
-        // 64 KB fit the instruction cache: 257 random cells 4.9 ms against 6.0.) ----
+        // 64 KB fit the instruction cache: 257 random cells 4.8 ms against 6.0.) ----
         int act = NONE, fin = -1;      // fin >= 0: the cell ends with this status
         double eta = 1.0;
         bool restore = false, fail = S.phase == LUFAIL;
