@@ -208,16 +208,24 @@ bool fused_ok(const chem_surr_s *s)
 int group_n(const chem_surr_s *s, int l) { return s->G == 1 || l == 0 ? s->out_l[l] : (l == 3 ? 1 : s->hg[l]); }
 bool grouped(const chem_surr_s *s, int l) { return s->G > 1 && l > 0; }
 
-// The fragment-order copy of the weights, made when they changed.
-hipError_t ensure_frag(chem_surr_s *s, hipStream_t st)
+// The fragment-order copy of the weights, made when they changed.  What a
+// captured stream is given runs only with the graph: it does not count as made,
+// and with `record` the graph makes the copy itself in every replay, from the
+// weights of that time.
+hipError_t ensure_frag(chem_surr_s *s, hipStream_t st, bool record = false)
 {
-    if (s->frag_valid) return hipSuccess;
+    if (s->frag_valid && !record) return hipSuccess;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    hipError_t q = hipStreamIsCapturing(st, &cs);
+    if (q != hipSuccess) return q;
+    const bool captured = cs != hipStreamCaptureStatusNone;
+    if (s->frag_valid && !captured) return hipSuccess;
     for (int l = 0; l < 4; l++) {
         hipError_t e = chem::launch_swizzle_frag(s->wbf + s->off_W[l], s->out_l[l], s->in_l[l],
                                                  s->wfrag + s->off_W[l], st);
         if (e != hipSuccess) return e;
     }
-    s->frag_valid = true;
+    if (!captured) s->frag_valid = true;
     return hipSuccess;
 }
 
@@ -251,6 +259,7 @@ hipError_t forward(chem_surr_s *s, const bf16_t *X, int rows, bf16_t *const H[3]
     if (!U[0] && !layered && fused_ok(s)) return forward_fused(s, X, rows, OUT, ldo, st);
     const bf16_t *in = X;
     hipError_t e = hipSuccess;
+    bool frag = false;   // this pass has seen to the fragments
     for (int l = 0; l < 4 && e == hipSuccess; l++) {
         const int N = s->out_l[l], Kd = s->in_l[l], ld_in = s->ain[l];
         const bool last = l == 3;
@@ -261,7 +270,8 @@ hipError_t forward(chem_surr_s *s, const bf16_t *X, int rows, bf16_t *const H[3]
         const int groups = grouped(s, l) ? s->G : 1;
         if (!last && !outf && ((uintptr_t)in | (uintptr_t)outh) % 16 == 0 &&
             chem::layer_forward_supported(rows, N / groups, Kd, groups)) {
-            e = ensure_frag(s, st);
+            if (!frag) e = ensure_frag(s, st, true);
+            frag = true;
             if (e == hipSuccess)
                 e = chem::launch_layer_forward(chem::LayerArgs{in, ld_in, Kd, s->wfrag + s->off_W[l],
                                                                s->master + s->off_b[l], rows, N / groups, Kd, groups,
