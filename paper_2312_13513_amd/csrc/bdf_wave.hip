@@ -1181,6 +1181,7 @@ static hipError_t launch_groups(Kern kern, int cells_per_wave, size_t dyn, bool 
                                 double dt, const BdfParams &prm, int32_t *status, int32_t *counters,
                                 unsigned long long *queue, double *qscratch, int max_groups, hipStream_t s)
 {
+    if (qglobal && (!qscratch || max_groups < cells_per_wave)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(reset_queue_kernel, dim3(1), dim3(1), 0, s, queue);
     int blocks = 0;
     {
@@ -1231,6 +1232,26 @@ bool wave_uses_global_scratch(const DevMechView &m, int lanes)
     const size_t q7 = (size_t)m.qstride * sizeof(double);
     if (lanes == 16) return (size_t)m.table_bytes + 4 * q7 > kTileStageMax;
     return wave_scratch_bytes(m) > kWaveLdsMax;
+}
+
+void set_view_sizes(DevMechView &m, int K, int R, int n_pdep, int32_t table_bytes)
+{
+    m.K = K;
+    m.R = R;
+    m.n_pdep = n_pdep;
+    m.table_bytes = table_bytes;
+    // 7 R doubles, one R more for the third-body derivatives when a reaction is
+    // pressure dependent
+    m.qstride = (n_pdep ? 8 : 7) * (R > 0 ? R : 1);
+}
+
+int wave_scratch_slots(const DevMechView &m, size_t bytes)
+{
+    const bool need = (wave_kernel_rows(m.K + 1) > 0 && wave_uses_global_scratch(m, 64)) ||
+                      (m.K + 1 <= 16 && wave_uses_global_scratch(m, 16));
+    if (!need) return 0;
+    const size_t slots = bytes / ((size_t)m.qstride * sizeof(double));
+    return (int)(slots < 4096 ? (slots < 64 ? 64 : slots) : 4096);
 }
 #endif
 

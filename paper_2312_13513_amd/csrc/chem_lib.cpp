@@ -231,6 +231,7 @@ int integrate_cells(chem_mech m, double *T, const double *p, double *Y, int64_t 
         const int lanes = sched == 2 ? 16 : 64;
         double *qs = nullptr;
         if (chem::wave_uses_global_scratch(m->view, lanes)) {
+            if (!m->wave_scratch) return fail(CHEM_EHIP, "the mechanism's handle holds no reaction scratch");
             // calls in flight on different streams take different partitions
             const unsigned part = __atomic_fetch_add(&m->next_part, 1u, __ATOMIC_RELAXED) % kScratchParts;
             qs = m->wave_scratch + (size_t)part * m->wave_slots * m->view.qstride;
@@ -415,22 +416,11 @@ int chem_load_mechanism(const char *path, int device, chem_mech *out)
         wtab = chem::build_wave_tables(K, rx, R, inc_lists, species, W, aux, nullptr, m->wave64);
     const size_t off_ws = (off_wt + wtab.size() + 255) & ~size_t(255);
     // global reaction scratch, only when a wave or tile variant needs it:
-    // kScratchParts partitions of up to 4096 slices (cells in flight)
-    chem::DevMechView probe{};
-    probe.K = K;
-    probe.R = R;
-    probe.table_bytes = (int32_t)table_bytes;
-    // reaction scratch of the lane-group kernels: 7 R doubles, one R more
-    // for the third-body derivatives when a reaction is pressure dependent
-    probe.qstride = (n_pdep ? 8 : 7) * (R > 0 ? R : 1);
-    const size_t slice = (size_t)probe.qstride * sizeof(double);
-    const bool need_ws = (chem::wave_kernel_rows(K + 1) > 0 && chem::wave_uses_global_scratch(probe, 64)) ||
-                         (K + 1 <= 16 && chem::wave_uses_global_scratch(probe, 16));
-    int wave_slots = 0;
-    if (need_ws) {
-        size_t slots = kScratchBudget / (kScratchParts * slice);
-        wave_slots = (int)(slots < 4096 ? (slots < 64 ? 64 : slots) : 4096);
-    }
+    // kScratchParts partitions of up to 4096 slices (cells in flight), by the
+    // view that the launches read
+    chem::set_view_sizes(m->view, K, R, n_pdep, (int32_t)table_bytes);
+    const size_t slice = (size_t)m->view.qstride * sizeof(double);
+    const int wave_slots = chem::wave_scratch_slots(m->view, kScratchBudget / kScratchParts);
     const size_t total = off_ws + (size_t)kScratchParts * wave_slots * slice;
     int prev = 0;
     if ((rc = check_hip(hipGetDevice(&prev), "hipGetDevice")) != CHEM_OK) {
@@ -468,17 +458,12 @@ int chem_load_mechanism(const char *path, int device, chem_mech *out)
         return rc;
     }
     m->dev_block = blk;
-    m->view.K = K;
-    m->view.R = R;
     m->view.two_range = two_range ? 1 : 0;
     m->view.species = (const double *)blk;
     m->view.W = (const double *)(blk + off_w);
     m->view.invW = (const double *)(blk + off_iw);
     m->view.rxn = (const chem::DevRxn *)(blk + off_rx);
-    m->view.table_bytes = (int32_t)table_bytes;
     m->view.aux = (const double *)(blk + off_aux);
-    m->view.n_pdep = n_pdep;
-    m->view.qstride = probe.qstride;
     m->queues = (unsigned long long *)(blk + off_q);
     m->wave.inc_off = (const int *)(blk + off_io);
     m->wave.inc = (const int2 *)(blk + off_inc);

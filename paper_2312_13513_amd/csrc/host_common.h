@@ -81,9 +81,10 @@ struct chem_mech_s {
     std::string variant = "table";
     chem::WaveTables wave{};                // species -> reaction incidence (tile kernel)
     chem::Wave64Tables wave64{};            // lane-by-lane tables of the wave kernel
-    // reaction scratch of the kernels whose 7 R doubles per cell in flight do
-    // not fit in LDS: kScratchParts partitions of wave_slots slices, one
-    // partition per call in rotation (NULL when no variant needs it)
+    // reaction scratch of the kernels whose share per cell in flight does not
+    // fit in LDS (wave_uses_global_scratch): kScratchParts partitions of wave_slots
+    // slices of view.qstride doubles, one partition per call in rotation (NULL
+    // when no variant needs it)
     double *wave_scratch = nullptr;
     int wave_slots = 0;
     unsigned next_part = 0;
