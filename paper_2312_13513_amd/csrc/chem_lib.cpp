@@ -166,6 +166,45 @@ bool is_device_ptr(const void *p)
 
 namespace chem_host {
 
+namespace {
+
+// The schedule a call of `items` cells runs.
+void pick_schedule(chem_mech m, chem_opts &o, int64_t items)
+{
+    if (o.schedule == -2) {
+        // the tuned choice of this call's size class, else of the nearest tuned one
+        Tuned t;
+        bool have = false;
+        {
+            std::lock_guard<std::mutex> lk(m->ws_mu);
+            const Tuned *tu = m->find_tuned(o.precision == 1 ? 1 : 0, size_class(items));
+            if (tu) {
+                t = *tu;
+                have = true;
+            }
+        }
+        o.schedule = have ? t.schedule : -1;
+        if (have && o.jac_batch == 0) o.jac_batch = t.jac_batch;
+        if (have && o.waves_per_simd == 0) o.waves_per_simd = t.waves_per_simd;
+    }
+    // automatic choice: one thread per cell for a compiled-in mechanism
+    // (state in registers and LDS, no spill), else the 16-lane tile when a
+    // cell fits in it (N <= 16), else one wave per cell
+    if (o.schedule < 0) o.schedule = m->gen && o.precision == 0 ? 0 : (m->host.K + 1 <= 16 ? 2 : 1);
+}
+
+}  // namespace
+
+size_t start_ws_bytes(chem_mech m, const chem_opts *opts, int64_t items)
+{
+    if (!m->gen || items <= 0) return 0;
+    chem_opts o;
+    chem_default_opts(&o);
+    if (opts) o = *opts;
+    pick_schedule(m, o, items);
+    return o.schedule == 0 ? chem::start_pass_bytes(m->host.K + 1, items) : 0;
+}
+
 int integrate_cells(chem_mech m, double *T, const double *p, double *Y, int64_t ldY, int64_t n,
                     double dt, const chem_opts *opts, int32_t *status, int32_t *counters,
                     hipStream_t stream, const int64_t *n_dev, const int32_t *idx, int64_t n_idx,
@@ -181,23 +220,7 @@ int integrate_cells(chem_mech m, double *T, const double *p, double *Y, int64_t 
     if (o.precision != 0 && o.precision != 1) return fail(CHEM_EINVAL, "precision must be 0 or 1");
     if (o.schedule < -2 || o.schedule > 2) return fail(CHEM_EINVAL, "unknown schedule");
     if (o.waves_per_simd < 0) return fail(CHEM_EINVAL, "waves_per_simd must be >= 0");
-    if (o.schedule == -2) {
-        // the tuned choice of this call's size class, else of the nearest tuned one
-        const int64_t items = idx ? n_idx : n;
-        Tuned t;
-        bool have = false;
-        {
-            std::lock_guard<std::mutex> lk(m->ws_mu);
-            const Tuned *tu = m->find_tuned(o.precision == 1 ? 1 : 0, size_class(items));
-            if (tu) {
-                t = *tu;
-                have = true;
-            }
-        }
-        o.schedule = have ? t.schedule : -1;
-        if (have && o.jac_batch == 0) o.jac_batch = t.jac_batch;
-        if (have && o.waves_per_simd == 0) o.waves_per_simd = t.waves_per_simd;
-    }
+    pick_schedule(m, o, idx ? n_idx : n);
     if (o.block != 0 && o.block != 64) return fail(CHEM_EUNSUP, "block must be 0 or 64");
     if (n == 0) return CHEM_OK;
     if ((status && !is_device_ptr(status)) || (counters && !is_device_ptr(counters)))
@@ -205,10 +228,7 @@ int integrate_cells(chem_mech m, double *T, const double *p, double *Y, int64_t 
     const int K = m->host.K;
     const bool thread_ok = m->gen != nullptr;
     const bool wave_ok = chem::wave_kernel_rows(K + 1) > 0;
-    // automatic choice: one thread per cell for a compiled-in mechanism
-    // (state in registers and LDS, no spill), else the 16-lane tile when a
-    // cell fits in it (N <= 16), else one wave per cell
-    const int sched = o.schedule >= 0 ? o.schedule : (m->gen && o.precision == 0 ? 0 : (K + 1 <= 16 ? 2 : 1));
+    const int sched = o.schedule;
     if (sched == 0 && !thread_ok)
         return fail(CHEM_EUNSUP, "the one-thread-per-cell schedule needs a compiled-in mechanism (list the "
                                  ".mech file in CHEM_EXTRA_MECHS when building)");

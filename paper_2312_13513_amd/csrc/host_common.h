@@ -138,6 +138,11 @@ int integrate_cells(chem_mech m, double *T, const double *p, double *Y, int64_t 
                     hipStream_t stream, const int64_t *n_dev, const int32_t *idx = nullptr,
                     int64_t n_idx = 0, void *fixed_ws = nullptr, size_t fixed_bytes = 0);
 
+// Bytes of start-pass workspace such a call of `items` cells uses (0 where its
+// schedule has no start pass): what a caller with a workspace of its own passes
+// as fixed_ws.
+size_t start_ws_bytes(chem_mech m, const chem_opts *opts, int64_t items);
+
 // Tuning cache file (CHEM_TUNE_CACHE): append one result, and restore the
 // lines of this mechanism file and architecture into the handle.
 void tune_cache_append(const chem_mech_s *m, int precision, int cls, const Tuned &t);

@@ -2,6 +2,7 @@
 // workspaces, the forward/backward/Adam sequence, training loop, inference
 // with per-cell fallback to the integrator, and the weights file.
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -100,8 +101,10 @@ struct chem_surr_s {
     // join, one per stream
     hipStream_t side[kSides] = {};
     hipEvent_t fork[kSides] = {}, joined[kSides] = {};
+    // start-pass workspace of each stream's integrations (compiled-in mechanisms),
+    // a pass's cells each, sized with the rest of the inference workspace
+    DevBuf side_ws[kSides];
     DevBuf pcount;                    // per-pass fallback counts
-    int64_t pcount_len = 0;
 };
 
 namespace {
@@ -756,6 +759,7 @@ void chem_free_surrogate(chem_surr s)
     s->fb.release();
     s->io.release();
     s->pcount.release();
+    for (DevBuf &b : s->side_ws) b.release();
     free_sides(s);
     if (s->block) hipFree(s->block);
     hipSetDevice(prev);
@@ -936,17 +940,20 @@ namespace {
 
 // Workspace of an inference call over n cells: the encoded rows and outputs
 // of one pass (fused forward) or every activation of one pass (per-layer
-// GEMMs), and the fallback compaction buffers for all n cells.
+// GEMMs), the fallback compaction buffers for all n cells, the counts of the
+// passes and the integrator's workspace of the side streams.
 struct InferWork {
     bool fused = false;
     int64_t chunk = 0;   // rows per pass
+    int sides = 0;       // side streams the passes take in turn
+    int64_t *pcount = nullptr;
     bf16_t *X = nullptr;
     float *OUT = nullptr;
     Acts a{};
     Fallback fb{};
 };
 
-int infer_workspace(chem_surr_s *s, int64_t n, hipStream_t st, InferWork &w)
+int infer_workspace(chem_surr_s *s, int64_t n, const chem_opts *opts, hipStream_t st, InferWork &w)
 {
     // the fused forward needs only the encoded rows and the outputs, so it
     // takes larger passes; the layered GEMMs keep every activation
@@ -971,7 +978,24 @@ int infer_workspace(chem_surr_s *s, int64_t n, hipStream_t st, InferWork &w)
         w.X = w.a.X;
         w.OUT = w.a.OUT;
     }
-    return ensure_fb(s, n, w.fb, st);
+    rc = ensure_fb(s, n, w.fb, st);
+    if (rc != CHEM_OK) return rc;
+    const int64_t npass = (n + w.chunk - 1) / w.chunk;
+    rc = s->pcount.grow(carve_size<int64_t>(npass), st);
+    if (rc != CHEM_OK) return rc;
+    w.pcount = (int64_t *)s->pcount.p;
+    // the last pass may be smaller, and its tuned schedule another one
+    const size_t need = std::max(chem_host::start_ws_bytes(s->mech, opts, rows),
+                                 chem_host::start_ws_bytes(s->mech, opts, n - (npass - 1) * w.chunk));
+    const int sides = s->mech->wave_scratch ? 1 : (int)std::min<int64_t>(npass, kSides);
+    for (w.sides = 0; w.sides < sides; w.sides++) {
+        rc = s->side_ws[w.sides].grow(need, st);
+        // one stream does for all passes where a second one's workspace is not to be
+        // had (the call is captured and only one was sized, or no memory is left)
+        if (rc != CHEM_OK && w.sides == 0) return rc;
+        if (rc != CHEM_OK) break;
+    }
+    return CHEM_OK;
 }
 
 }  // namespace
@@ -983,7 +1007,7 @@ int chem_surrogate_reserve(chem_surr s, int64_t ncells, void *stream)
     if (ncells < 0 || ncells > INT32_MAX) return fail(CHEM_EINVAL, "ncells must be in 0..2^31-1");
     if (ncells == 0) return CHEM_OK;
     InferWork w;
-    return infer_workspace(s, ncells, (hipStream_t)stream, w);
+    return infer_workspace(s, ncells, nullptr, (hipStream_t)stream, w);
 }
 
 int chem_surrogate_set_pass_rows(chem_surr s, int64_t rows)
@@ -1016,7 +1040,7 @@ int chem_surrogate_infer(chem_surr s, double *T, const double *p, double *Y, int
     const int K = s->K;
     hipStream_t st = (hipStream_t)stream;
     InferWork w;
-    rc = infer_workspace(s, n, st, w);
+    rc = infer_workspace(s, n, opts, st, w);
     if (rc != CHEM_OK) return rc;
     const bool fused = w.fused;
     const int64_t chunk = w.chunk;
@@ -1030,16 +1054,11 @@ int chem_surrogate_infer(chem_surr s, double *T, const double *p, double *Y, int
     // its rr rows), gathered into fb.T/p/Y/status[r0 ..] and integrated on
     // the side stream as soon as the pass is applied
     const int64_t npass = (n + chunk - 1) / chunk;
-    if (npass > s->pcount_len) {
-        rc = s->pcount.grow(carve_size<int64_t>(npass), st);
-        if (rc != CHEM_OK) return rc;
-        s->pcount_len = npass;
-    }
-    int64_t *pc = (int64_t *)s->pcount.p;
+    int64_t *pc = w.pcount;
     rc = check_hip(chem::launch_zero_i64(pc, (int)npass, st), "zero");
     if (rc != CHEM_OK) return rc;
     const chem::ApplyArgs aa = apply_args(s, c);
-    const int sides = s->mech->wave_scratch ? 1 : kSides;
+    const int sides = w.sides;
     int64_t q = 0;
     for (int64_t r0 = 0; r0 < n; r0 += chunk, q++) {
         const int rr = (int)(n - r0 < chunk ? n - r0 : chunk);
@@ -1062,14 +1081,15 @@ int chem_surrogate_infer(chem_surr s, double *T, const double *p, double *Y, int
                            "gather");
         if (rc == CHEM_OK)
             rc = chem_host::integrate_cells(s->mech, fb.T + r0, fb.p + r0, fb.Y + r0, fb.cap, rr, dt, opts,
-                                            fb.status + r0, nullptr, sd, pc + q);
+                                            fb.status + r0, nullptr, sd, pc + q, nullptr, 0,
+                                            s->side_ws[q % sides].p, s->side_ws[q % sides].bytes);
         if (rc == CHEM_OK)
             rc = check_hip(chem::launch_scatter_cells_ld(fb.list + r0, pc + q, rr, fb.cap, fb.T + r0, fb.Y + r0,
                                                          fb.status + r0, K, T, Y, ldY, status, sd),
                            "scatter");
         if (rc != CHEM_OK) return rc;
     }
-    for (int i = 0; i < sides && i < npass && rc == CHEM_OK; i++) {
+    for (int i = 0; i < sides && rc == CHEM_OK; i++) {
         rc = check_hip(hipEventRecord(s->joined[i], s->side[i]), "join event");
         if (rc == CHEM_OK) rc = check_hip(hipStreamWaitEvent(st, s->joined[i], 0), "join wait");
     }
