@@ -48,7 +48,7 @@ hipError_t launch_gemm_bf16(const GemmArgs &g, hipStream_t s);
 
 // One GELU layer of inference, `groups` networks side by side: rows of N units
 // H[m][z N + n] = bf16(gelu(sum_k A[m][z za + k] W_z[n][k] + bias[z N + n])), W in
-// fragment order (launch_swizzle_frag of the [groups N][K] matrix).  N and K
+// fragment order (UpdateArgs::wfrag of the [groups N][K] matrix).  N and K
 // multiples of 64, lda, za and ldh multiples of 8, A, H and bias 16-byte
 // aligned.  The bits of launch_gemm_bf16's products.
 struct LayerArgs {
@@ -67,7 +67,7 @@ hipError_t launch_layer_forward(const LayerArgs &a, hipStream_t s);
 
 // Fused inference forward pass: out = W4 h3 + b4 with h_l = GELU(W_l h_(l-1) + b_l),
 // h_0 = the 64-wide input rows.  W[l] holds the [out_l][in_l] BF16 weights in
-// fragment order (launch_swizzle_frag; in_l of layer 0 is 64), b[l] FP32.
+// fragment order (UpdateArgs::wfrag; in_l of layer 0 is 64), b[l] FP32.
 // One block takes 32 rows through all four layers with the activations in
 // LDS; the result equals the layer-by-layer GEMMs bit for bit.
 struct MlpArgs {
@@ -81,8 +81,6 @@ struct MlpArgs {
 };
 // false when the hidden widths do not fit the fused kernel (each <= 512).
 bool mlp_fused_supported(const int out_l[4]);
-// W [N][K] row-major -> Wf in the fused kernel's fragment order (N % 16 == 0, K % 32 == 0).
-hipError_t launch_swizzle_frag(const bf16_t *W, int N, int K, bf16_t *Wf, hipStream_t s);
 hipError_t launch_mlp_forward(const MlpArgs &a, hipStream_t s);
 
 // Network input of cells: x = zscore([T, p, BoxCox(max(Y,0); 0.1)]) -> FP32 -> BF16,
@@ -160,6 +158,5 @@ struct AdamArgs {
     float lr, beta1, beta2, omb1, omb2, eps, bc1, bc2;
 };
 hipError_t launch_adam(const AdamArgs &a, hipStream_t s);
-hipError_t launch_to_bf16(const float *src, bf16_t *dst, int64_t n, hipStream_t s);
 
 }  // namespace chem

@@ -313,7 +313,7 @@ __global__ void __launch_bounds__(256, 2) layer_forward_kernel(LayerArgs a)
 // activations) from LDS and B (the weights, L2-resident) loaded by each lane
 // straight into its MFMA operand registers.  Wave w owns the 16-column blocks
 // w + 4 j of the layer's output for both 16-row blocks, so every weight
-// fragment is loaded once per block.  The weights come in fragment order (swizzle_frag_kernel): the
+// fragment is loaded once per block.  The weights come in fragment order (UpdateArgs): the
 // 16 x 32 operand of column block jb and K step ks is 1 KB at
 // ((jb * K/32 + ks) * 512 + 8 lane), so a wave reads it as one contiguous
 // 16-byte-per-lane load.  The accumulation over K runs in steps of 32 in
@@ -444,20 +444,6 @@ __device__ __forceinline__ void mlp_layer_any(const bf16_t *in, int ldi, int K, 
         mlp_layer<kMlpJ>(in, ldi, K, Wf, N, bias, outs, lds_out, outg, ldg, r0, rows);
     }
 #undef CHEM_MLP_LAYER
-}
-
-// Weights [N][K] -> fragment order (see above), 8 values per thread.
-__global__ void __launch_bounds__(256) swizzle_frag_kernel(const bf16_t *__restrict__ W, int N, int K,
-                                                           bf16_t *__restrict__ Wf)
-{
-    const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // 8-value chunk of Wf
-    if (c >= (int64_t)N * K / 8) return;
-    const int64_t blk = c >> 6;
-    const int L = (int)(c & 63);
-    const int ksteps = K >> 5;
-    const int jb = (int)(blk / ksteps), ks = (int)(blk % ksteps);
-    const int n = jb * 16 + (L & 15), k = ks * 32 + (L >> 4) * 8;
-    *(uint4 *)(Wf + c * 8) = *(const uint4 *)(W + (int64_t)n * K + k);
 }
 
 __global__ void __launch_bounds__(64 * kMlpWaves, 3) mlp_forward_kernel(MlpArgs a)
@@ -918,13 +904,6 @@ __global__ void __launch_bounds__(256) adam_kernel(AdamArgs a)
     a.p[i] -= a.lr * mh / (sqrtf(vh) + a.eps);
 }
 
-__global__ void __launch_bounds__(256) to_bf16_kernel(const float *__restrict__ src,
-                                                      bf16_t *__restrict__ dst, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = to_bf16(src[i]);
-}
-
 }  // namespace
 
 hipError_t launch_gemm_bf16(const GemmArgs &g, hipStream_t s)
@@ -982,14 +961,6 @@ bool mlp_fused_supported(const int out_l[4])
         hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
         return false;
     return mlp_lds_bytes(out_l) <= (size_t)max_lds;
-}
-
-hipError_t launch_swizzle_frag(const bf16_t *W, int N, int K, bf16_t *Wf, hipStream_t s)
-{
-    if (N % 16 != 0 || K % 32 != 0) return hipErrorInvalidValue;
-    const int64_t chunks = (int64_t)N * K / 8;
-    hipLaunchKernelGGL(swizzle_frag_kernel, dim3(blocks_for(chunks, 256)), dim3(256), 0, s, W, N, K, Wf);
-    return hipGetLastError();
 }
 
 hipError_t launch_mlp_forward(const MlpArgs &a, hipStream_t s)
@@ -1160,13 +1131,6 @@ hipError_t launch_adam(const AdamArgs &a, hipStream_t s)
 {
     if (a.n <= 0) return hipSuccess;
     hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(a.n, 256)), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_to_bf16(const float *src, bf16_t *dst, int64_t n, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, src, dst, n);
     return hipGetLastError();
 }
 

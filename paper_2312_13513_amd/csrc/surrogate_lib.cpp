@@ -65,12 +65,13 @@ struct chem_surr_s {
     int ain[4];                       // width of each layer's input activations (G in_l for grouped layers)
     int64_t off_W[4], off_b[4], n_pad = 0, n_logical = 0;
     float *master = nullptr, *grad = nullptr, *am = nullptr, *av = nullptr;
-    bf16_t *wbf = nullptr;
-    bf16_t *wfrag = nullptr;          // the BF16 weights in the fused kernel's fragment order
-    bool frag_valid = false;          // wfrag matches wbf
-    bf16_t *wfragT = nullptr;         // the transposes of layers 2..4 in that order (training, see train_fused)
+    // the BF16 weights row by row, in the forward kernels' fragment order and, for
+    // the fused training, the transposes of layers 2..4 in that order.  Whatever
+    // changes the parameters writes all of them on its stream (refresh_weights,
+    // train_batch): no forward pass has to, and a captured one uses the weights of
+    // the time of its replay
+    bf16_t *wbf = nullptr, *wfrag = nullptr, *wfragT = nullptr;
     int64_t off_T[4] = {0, 0, 0, 0};
-    bool fragT_valid = false;         // wfragT matches wbf
     DevBuf tr;                        // activations and errors of a batch (train_fused)
     int64_t tr_rows = 0;
     double *norm_dev = nullptr;       // mu_x, sig_x, mu_y, sig_y
@@ -211,34 +212,11 @@ bool fused_ok(const chem_surr_s *s)
 int group_n(const chem_surr_s *s, int l) { return s->G == 1 || l == 0 ? s->out_l[l] : (l == 3 ? 1 : s->hg[l]); }
 bool grouped(const chem_surr_s *s, int l) { return s->G > 1 && l > 0; }
 
-// The fragment-order copy of the weights, made when they changed.  What a
-// captured stream is given runs only with the graph: it does not count as made,
-// and with `record` the graph makes the copy itself in every replay, from the
-// weights of that time.
-hipError_t ensure_frag(chem_surr_s *s, hipStream_t st, bool record = false)
-{
-    if (s->frag_valid && !record) return hipSuccess;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    hipError_t q = hipStreamIsCapturing(st, &cs);
-    if (q != hipSuccess) return q;
-    const bool captured = cs != hipStreamCaptureStatusNone;
-    if (s->frag_valid && !captured) return hipSuccess;
-    for (int l = 0; l < 4; l++) {
-        hipError_t e = chem::launch_swizzle_frag(s->wbf + s->off_W[l], s->out_l[l], s->in_l[l],
-                                                 s->wfrag + s->off_W[l], st);
-        if (e != hipSuccess) return e;
-    }
-    if (!captured) s->frag_valid = true;
-    return hipSuccess;
-}
-
 // Inference forward pass of all four layers in one kernel (activations in
 // LDS).
-hipError_t forward_fused(chem_surr_s *s, const bf16_t *X, int64_t rows, float *OUT, int64_t ldo,
+hipError_t forward_fused(const chem_surr_s *s, const bf16_t *X, int64_t rows, float *OUT, int64_t ldo,
                          hipStream_t st)
 {
-    hipError_t e = ensure_frag(s, st);
-    if (e != hipSuccess) return e;
     chem::MlpArgs a{};
     a.X = X;
     a.rows = rows;
@@ -256,13 +234,12 @@ hipError_t forward_fused(chem_surr_s *s, const bf16_t *X, int64_t rows, float *O
 // Forward pass of `rows` rows of X; saves pre-activations when U[0] != NULL.
 // Without saved pre-activations the fused kernel runs when the widths allow
 // it (the same result bit for bit), unless `layered` asks for the GEMMs.
-hipError_t forward(chem_surr_s *s, const bf16_t *X, int rows, bf16_t *const H[3],
+hipError_t forward(const chem_surr_s *s, const bf16_t *X, int rows, bf16_t *const H[3],
                    float *const U[3], float *OUT, int64_t ldo, hipStream_t st, bool layered = false)
 {
     if (!U[0] && !layered && fused_ok(s)) return forward_fused(s, X, rows, OUT, ldo, st);
     const bf16_t *in = X;
     hipError_t e = hipSuccess;
-    bool frag = false;   // this pass has seen to the fragments
     for (int l = 0; l < 4 && e == hipSuccess; l++) {
         const int N = s->out_l[l], Kd = s->in_l[l], ld_in = s->ain[l];
         const bool last = l == 3;
@@ -273,13 +250,10 @@ hipError_t forward(chem_surr_s *s, const bf16_t *X, int rows, bf16_t *const H[3]
         const int groups = grouped(s, l) ? s->G : 1;
         if (!last && !outf && ((uintptr_t)in | (uintptr_t)outh) % 16 == 0 &&
             chem::layer_forward_supported(rows, N / groups, Kd, groups)) {
-            if (!frag) e = ensure_frag(s, st, true);
-            frag = true;
-            if (e == hipSuccess)
-                e = chem::launch_layer_forward(chem::LayerArgs{in, ld_in, Kd, s->wfrag + s->off_W[l],
-                                                               s->master + s->off_b[l], rows, N / groups, Kd, groups,
-                                                               outh, N},
-                                               st);
+            e = chem::launch_layer_forward(chem::LayerArgs{in, ld_in, Kd, s->wfrag + s->off_W[l],
+                                                           s->master + s->off_b[l], rows, N / groups, Kd, groups,
+                                                           outh, N},
+                                           st);
         } else if (!grouped(s, l)) {
             e = gemm(in, ld_in, 1, s->wbf + s->off_W[l], Kd, 1, rows, N, Kd, epi, s->master + s->off_b[l], outf,
                      ldf, outh, N, nullptr, 0, st);
@@ -377,7 +351,7 @@ chem::UpdateArgs update_args(const chem_surr_s *s)
     u.o.p = s->master;
     u.wbf = s->wbf;
     u.wfrag = s->wfrag;
-    u.wfragT = s->wfragT;
+    u.wfragT = train_fused(s) ? s->wfragT : nullptr;
     for (int l = 0; l < 4; l++) {
         u.in_l[l] = s->in_l[l];
         u.out_l[l] = s->out_l[l];
@@ -392,14 +366,6 @@ chem::UpdateArgs update_args(const chem_surr_s *s)
 hipError_t train_batch(chem_surr_s *s, const bf16_t *X, const int32_t *order, int64_t start, int64_t rows,
                        const float *Y, int64_t ldy, const chem::AdamArgs *adam, hipStream_t st)
 {
-    hipError_t e = hipSuccess;
-    if (!s->frag_valid || !s->fragT_valid) {
-        chem::UpdateArgs u = update_args(s);
-        u.weights = 1;
-        e = chem::launch_train_update(u, st);
-        if (e != hipSuccess) return e;
-        s->frag_valid = s->fragT_valid = true;
-    }
     size_t bytes = 0;
     const TrainBuf b = carve_train(s, s->tr_rows, (char *)s->tr.p, bytes);
     chem::TrainArgs t{};
@@ -436,7 +402,7 @@ hipError_t train_batch(chem_surr_s *s, const bf16_t *X, const int32_t *order, in
         g.off_W[l] = s->off_W[l];
         g.off_b[l] = s->off_b[l];
     }
-    e = chem::launch_train_rows(t, st);
+    hipError_t e = chem::launch_train_rows(t, st);
     if (e == hipSuccess) e = chem::launch_train_grad(g, st);
     if (e != hipSuccess) return e;
     chem::UpdateArgs u = update_args(s);
@@ -510,10 +476,12 @@ int download_logical(chem_surr_s *s, const float *dev, float *host, int64_t coun
     return CHEM_OK;
 }
 
-int refresh_bf16(chem_surr_s *s, hipStream_t st)
+// The BF16 weights in all their orders from the parameters.
+hipError_t refresh_weights(const chem_surr_s *s, hipStream_t st)
 {
-    s->frag_valid = s->fragT_valid = false;
-    return check_hip(chem::launch_to_bf16(s->master, s->wbf, s->n_pad, st), "bf16 weights");
+    chem::UpdateArgs u = update_args(s);
+    u.weights = 1;
+    return chem::launch_train_update(u, st);
 }
 
 // Fallback compaction buffers for up to n cells: list, T, p, Y (K x cap), status.
@@ -785,7 +753,7 @@ int chem_surrogate_set_params(chem_surr s, const float *params, int64_t count)
     if (!params) return fail(CHEM_EINVAL, "params is NULL");
     rc = upload_logical(s, s->master, params, count);
     if (rc != CHEM_OK) return rc;
-    rc = refresh_bf16(s, nullptr);
+    rc = check_hip(refresh_weights(s, nullptr), "bf16 weights");
     if (rc != CHEM_OK) return rc;
     // a new parameter vector restarts the optimiser
     s->adam_t = 0;
@@ -1164,7 +1132,7 @@ int chem_surrogate_adam(chem_surr s, double lr, void *stream)
     hipStream_t st = (hipStream_t)stream;
     rc = check_hip(chem::launch_adam(a, st), "adam");
     if (rc != CHEM_OK) return rc;
-    return refresh_bf16(s, st);
+    return check_hip(refresh_weights(s, st), "bf16 weights");
 }
 
 int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, const double *Y, int64_t ldY,
@@ -1225,8 +1193,7 @@ int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, con
             if (e == hipSuccess) {
                 s->adam_t++;
                 e = chem::launch_adam(adam_args(s, lr), st);
-                if (e == hipSuccess) e = chem::launch_to_bf16(s->master, s->wbf, s->n_pad, st);
-                s->frag_valid = s->fragT_valid = false;
+                if (e == hipSuccess) e = refresh_weights(s, st);
             }
         }
         if (e == hipSuccess && loss_per_epoch) {

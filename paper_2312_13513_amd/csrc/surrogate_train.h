@@ -44,7 +44,12 @@ struct GradArgs {
 hipError_t launch_train_grad(const GradArgs &a, hipStream_t s);
 
 // With `weights` the BF16 copies of the parameters o.p, after an Adam step if
-// `adam`; *loss += the sum of loss_part (unless NULL).
+// `adam`; *loss += the sum of loss_part (unless NULL).  Layers of any width, in_l
+// multiples of 64 and out_l of 16.
+// wbf: row by row; wfrag: each layer's [out_l][in_l] matrix in fragment order, the
+// 16 x 32 operand of rows 16 jb .. and columns 32 ks .. as 512 values at
+// (jb in_l / 32 + ks) 512, lane by lane, 8 each; wfragT (unless NULL): the transposes
+// of layers 2..4 in that order, at off_T, their columns padded to 64.
 struct UpdateArgs {
     int64_t n_pad;
     int weights, adam;

@@ -373,7 +373,7 @@ __global__ void __launch_bounds__(64) adam_rows_kernel(UpdateArgs a)
     if (o >= (int64_t)a.out_l[l] * K) return;   // biases
     const int n = (int)(o / K), k = (int)(o % K);
     *(uint4 *)(a.wfrag + a.off_W[l] + frag_at(n, k, K)) = pk;
-    if (l > 0) {
+    if (l > 0 && a.wfragT) {
         const int Nt = (a.out_l[l] + 63) & ~63;
 #pragma unroll
         for (int e = 0; e < 8; e++) a.wfragT[a.off_T[l] + frag_at(k + e, n, Nt)] = h[e];
