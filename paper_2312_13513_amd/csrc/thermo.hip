@@ -401,7 +401,8 @@ __global__ void __launch_bounds__(grp_block(NG), 2) transport_group_kernel(const
                             S[G1] = fma(Xr[r], ib, S[G1]);
                             P[r] = fma(X[G1], ib, P[r]);
                         } else {
-                            P[r] = fma(q == r ? 0.0 : X[G1], ib, P[r]);
+                            // a species' own fit takes no part (it may have no reciprocal)
+                            P[r] = fma(X[G1], q == r ? 0.0 : ib, P[r]);
                         }
                     }
                 }
