@@ -133,7 +133,7 @@ __device__ __forceinline__ void load_yr(const double *__restrict__ Y, int64_t ld
 
 // MODE bit 1: viscosity and conductivity; bit 2: diffusion coefficients.
 // Every species loop unrolls and a cell's values stay in registers.
-template <int KM, int MODE, bool EX = false>
+template <int KM, int MODE>
 __global__ void __launch_bounds__(kThermoBlock) transport_kernel(TrView v, const double *__restrict__ T,
                                                                  const double *__restrict__ p,
                                                                  const double *__restrict__ Y, int64_t ldY,
@@ -595,16 +595,8 @@ hipError_t launch_transport_km(const TrView &v, const double *T, const double *p
                                int64_t n, double *mu, double *lam, double *D, int64_t ldD, hipStream_t st)
 {
     const dim3 g(blocks_for(n)), b(kThermoBlock);
-    const bool ex = v.K == KM;
-#define CHEM_TR_MODE(MODE)                                                                                     \
-    do {                                                                                                      \
-        if (ex)                                                                                               \
-            hipLaunchKernelGGL((transport_kernel<KM, MODE, true>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam,  \
-                               D, ldD);                                                                       \
-        else                                                                                                  \
-            hipLaunchKernelGGL((transport_kernel<KM, MODE, false>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam, \
-                               D, ldD);                                                                       \
-    } while (0)
+#define CHEM_TR_MODE(MODE) \
+    hipLaunchKernelGGL((transport_kernel<KM, MODE>), g, b, 0, st, v, T, p, Y, ldY, n, mu, lam, D, ldD)
     if (mu && D)
         CHEM_TR_MODE(3);
     else if (mu)
