@@ -927,12 +927,24 @@ static int64_t layer_tiles(int64_t M, int N, int groups)
     return (M + kLayerM - 1) / kLayerM * ((N + kLayerN - 1) / kLayerN) * groups;
 }
 
-// From 64 tiles on: 1,000 rows of the nine networks (8 row blocks; 456, 288 and
-// 144 tiles) 359 -> 272 us, 200 rows (114, 72 and 36 tiles, the last by the
-// general product) 258 -> 248; with fewer the 64 x 64 tiles have more blocks.
+// Against the 64 x 64 and 128 x 128 tiles of the general product, over widths 64
+// to 14,400, contractions 64 to 1,600 and 1 to 35 networks: the layer kernel's
+// fixed cost (its outputs pass through LDS once more) wants work to set against
+// it, active waves (64 units of 128 rows each) times the contraction: 64 deep it
+// breaks even at 390 waves, 128 deep at 260, 256 deep at 150.  A layer whose blocks
+// have fewer than three active waves in four (64, 128, 320 units) and a short
+// contraction needs several rounds of blocks to win (320 units, 64 deep: 304 blocks
+// 14.4 us against 12.8; 128 units: 384 blocks 14.4 against 12.2, 765 blocks 1.16
+// times faster); with one in four (64 units) it wins only while all blocks are
+// resident at once, two per CU (1,600 deep: 387 blocks 1.33 times faster, 513
+// blocks 77 us against 63).  Below 64 blocks the general tiles have more of them.
 bool layer_forward_supported(int64_t M, int N, int K, int groups)
 {
-    return N % 64 == 0 && K % kLayerK == 0 && layer_tiles(M, N, groups) >= 64;
+    if (N % 64 != 0 || K % kLayerK != 0) return false;
+    const int64_t blocks = layer_tiles(M, N, groups);
+    const int64_t waves = (M + kLayerM - 1) / kLayerM * (N / 64) * groups;
+    if (blocks < 64 || (N == 64 && blocks > 512)) return false;
+    return waves * (K + 64) >= (waves < 3 * blocks && K <= 128 ? 200000 : 50000);
 }
 
 hipError_t launch_layer_forward(const LayerArgs &a, hipStream_t s)
