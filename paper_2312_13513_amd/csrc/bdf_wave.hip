@@ -1204,17 +1204,25 @@ static hipError_t launch_groups(Kern kern, int cells_per_wave, size_t dyn, bool 
     return hipGetLastError();
 }
 
-constexpr size_t kWaveLdsMax = 49152;     // reaction scratch of one wave kept in LDS up to this size
+// The wave kernel's reaction scratch is in LDS up to this many bytes of qstride
+// doubles (877 elementary reactions, 768 with pressure-dependent ones).  The scratch
+// itself is smaller by now, but more of them in LDS leave too few waves on a CU:
+// 12,000 cells, 870 reactions with fall-off, 55 species 494 ms in LDS, 159 in global
+// memory (900 elementary, FP32 matrix, 45 species: 144 and 83); 64 cells, where no
+// second wave is wanted, 15.8 and 17.7.
+constexpr size_t kWaveLdsMax = 49152;
 constexpr size_t kTileStageMax = 24576;   // tables + scratch of a tile block staged in LDS up to this size
 constexpr int64_t kDeferMinCells = 65536; // tile batches from this size defer Newton-matrix refreshes
 
 // Reactions per lane the wave kernel holds in registers (0: more than 4).
 static int wave_regs(int R) { return R <= 128 ? 2 : R <= 256 ? 4 : 0; }
 
+static bool wave_global(const DevMechView &m) { return (size_t)m.qstride * sizeof(double) > kWaveLdsMax; }
+
 // Whether the wave schedule runs the tile's operations (bdf_small_wave_kernel).
 static bool wave_small(const DevMechView &m)
 {
-    return m.K + 1 <= 16 && (size_t)m.qstride * sizeof(double) <= kWaveLdsMax;
+    return m.K + 1 <= 16 && !wave_global(m);
 }
 
 // Bytes of the wave kernel's scratch (layout in wave_tables.h and
@@ -1231,7 +1239,7 @@ bool wave_uses_global_scratch(const DevMechView &m, int lanes)
 {
     const size_t q7 = (size_t)m.qstride * sizeof(double);
     if (lanes == 16) return (size_t)m.table_bytes + 4 * q7 > kTileStageMax;
-    return wave_scratch_bytes(m) > kWaveLdsMax;
+    return wave_global(m);
 }
 
 void set_view_sizes(DevMechView &m, int K, int R, int n_pdep, int32_t table_bytes)
@@ -1338,7 +1346,8 @@ hipError_t launch_bdf_wave(const DevMechView &m, const WaveTables &wt, const Wav
     }
     const int rpl = wave_regs(m.R);
     if (rpl == 0) {
-        if (wave_scratch_bytes(m) > kWaveLdsMax) CHEM_WAVE_LAUNCH(64, 0, , false);
+        if (wave_global(m) && N <= 48) CHEM_WAVE_LAUNCH(48, 0, , false);
+        if (wave_global(m)) CHEM_WAVE_LAUNCH(64, 0, , false);
         if (N <= 48) CHEM_WAVE_LAUNCH(48, 0);
         if (N <= 64) CHEM_WAVE_LAUNCH(64, 0);
         return hipErrorInvalidValue;

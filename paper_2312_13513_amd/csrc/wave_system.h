@@ -163,24 +163,31 @@ struct WaveSys {
         };
         // every table entry is fetched before the first sum and every value
         // read before the first addition, the quads counted at compile time
-        auto quads = [&](auto nc) __attribute__((always_inline)) {
+        auto quads = [&](auto nc, int i0 = 0) __attribute__((always_inline)) {
             constexpr int n = decltype(nc)::value;
             uint4 e[n];
 #pragma unroll
-            for (int i = 0; i < n; i++) e[i] = wt.gat[i * 64 + lane];
+            for (int i = 0; i < n; i++) e[i] = wt.gat[(i0 + i) * 64 + lane];
 #pragma unroll
             for (int i = 0; i < n; i++) add(e[i]);
         };
-        switch (wt.gather4) {
-        case 1: quads(std::integral_constant<int, 1>{}); break;
-        case 2: quads(std::integral_constant<int, 2>{}); break;
-        case 3: quads(std::integral_constant<int, 3>{}); break;
-        case 4: quads(std::integral_constant<int, 4>{}); break;
-        case 5: quads(std::integral_constant<int, 5>{}); break;
-        case 6: quads(std::integral_constant<int, 6>{}); break;
-        default:
+        if constexpr (RPL == 0) {
+            // many reactions: long sums, the more so from a scratch in global memory
+            int i = 0;
+            for (; i + 6 <= wt.gather4; i += 6) quads(std::integral_constant<int, 6>{}, i);
+            for (; i < wt.gather4; i++) quads(std::integral_constant<int, 1>{}, i);
+        } else {
+            switch (wt.gather4) {
+            case 1: quads(std::integral_constant<int, 1>{}); break;
+            case 2: quads(std::integral_constant<int, 2>{}); break;
+            case 3: quads(std::integral_constant<int, 3>{}); break;
+            case 4: quads(std::integral_constant<int, 4>{}); break;
+            case 5: quads(std::integral_constant<int, 5>{}); break;
+            case 6: quads(std::integral_constant<int, 6>{}); break;
+            default:
 #pragma clang loop unroll(disable)
-            for (int i = 0; i < wt.gather4; i++) add(wt.gat[i * 64 + lane]);
+                for (int i = 0; i < wt.gather4; i++) add(wt.gat[i * 64 + lane]);
+            }
         }
         L.part[lane] = s;
         sync();
@@ -227,15 +234,43 @@ struct WaveSys {
         return Slots{(int)(w & 63u), (int)(w >> 6 & 63u), (int)(w >> 12 & 63u), (int)(w >> 18 & 63u)};
     }
 
+    // f(i, record) for this lane's reactions i * 64 + lane.  Beyond the register
+    // builds each record is fetched ahead of the work on the one before: the compiler
+    // cannot move a table read over a write to a scratch in global memory.  (With the
+    // other fetches ahead below and 48 rows where they suffice: 12,000 cells of 45
+    // species and 900 elementary reactions 120 -> 93 ms, with FP32 matrix 97 -> 83.)
+    struct Record {
+        double2 ka, kb;
+        uint32_t w;
+    };
+    template <class F>
+    __device__ __forceinline__ void each_reaction(F &&f) const
+    {
+        auto fetch = [&](int i) __attribute__((always_inline)) {
+            return Record{wt.rx[(2 * i) * 64 + lane], wt.rx[(2 * i + 1) * 64 + lane], wt.rw[i * 64 + lane]};
+        };
+        if constexpr (RPL > 0) {
+#pragma unroll
+            for (int i = 0; i < RPL; i++) f(i, fetch(i));
+        } else {
+            Record rec = fetch(0);
+            for (int i = 0; i < wt.rounds; i++) {
+                const Record next = fetch(i + 1 < wt.rounds ? i + 1 : 0);
+                f(i, rec);
+                rec = next;
+            }
+        }
+    }
+
     // f(y): each lane passes its component yi and receives fi
     __device__ __forceinline__ double rhs(double p, double yi)
     {
         const Mix x = mixture(p, yi);
         const double ln_c0 = log(kPstd / kRu) - x.lnT;
-        auto rate = [&](int i) __attribute__((always_inline)) {
+        each_reaction([&](int i, const Record &rec) __attribute__((always_inline)) {
             const int r = i * 64 + lane;
-            const double2 ka = wt.rx[(2 * i) * 64 + lane], kb = wt.rx[(2 * i + 1) * 64 + lane];
-            const uint32_t w = wt.rw[r];
+            const double2 ka = rec.ka, kb = rec.kb;
+            const uint32_t w = rec.w;
             const Slots s = slots(w);
             const double lnkf = ka.x + ka.y * x.lnT - kb.x * x.invT;
             const double dg = L.g[s.p0] + L.g[s.p1] - L.g[s.r0] - L.g[s.r1];
@@ -254,13 +289,7 @@ struct WaveSys {
                 P[1 + r] = q;
                 P[1 + R + r] = -q;
             }
-        };
-        if constexpr (RPL > 0) {
-#pragma unroll
-            for (int i = 0; i < RPL; i++) rate(i);
-        } else {
-            for (int i = 0; i < wt.rounds; i++) rate(i);
-        }
+        });
         sync();
         const double w0 = produce();
         const double wk = lane < K ? w0 : 0.0;
@@ -283,10 +312,10 @@ struct WaveSys {
         // in the scratch), G = dq/d[M] of a pressure-dependent one
         double *gM = P + 1 + 4 * R, *kfs = gM + (kPD ? R : 0), *krs = kfs + R;
         double kfv[RPL > 0 ? RPL : 1], krv[RPL > 0 ? RPL : 1];
-        auto rates = [&](int i) __attribute__((always_inline)) {
+        each_reaction([&](int i, const Record &rec) __attribute__((always_inline)) {
             const int r = i * 64 + lane;
-            const double2 ka = wt.rx[(2 * i) * 64 + lane], kb = wt.rx[(2 * i + 1) * 64 + lane];
-            const uint32_t w = wt.rw[r];
+            const double2 ka = rec.ka, kb = rec.kb;
+            const uint32_t w = rec.w;
             const Slots s = slots(w);
             const double lnkf = ka.x + ka.y * x.lnT - kb.x * invT;
             const double dg = L.g[s.p0] + L.g[s.p1] - L.g[s.r0] - L.g[s.r1];
@@ -330,7 +359,7 @@ struct WaveSys {
                 kfs[r] = kf;
                 krs[r] = kr;
             }
-        };
+        });
         auto all = [&](auto &&f) __attribute__((always_inline)) {
             if constexpr (RPL > 0) {
 #pragma unroll
@@ -342,17 +371,28 @@ struct WaveSys {
         // production sums of q, qh and dq/dT: each value in turn at the two
         // places the production table reads
         auto move = [&](int from) __attribute__((always_inline)) {
-            all([&](int i) __attribute__((always_inline)) {
-                const int r = i * 64 + lane;
-                if (r < R) {
-                    const double v = P[1 + from * R + r];
-                    P[1 + r] = v;
-                    P[1 + R + r] = -v;
+            auto put = [&](int r, double v) __attribute__((always_inline)) {
+                P[1 + r] = v;
+                P[1 + R + r] = -v;
+            };
+            if constexpr (RPL > 0) {
+#pragma unroll
+                for (int i = 0; i < RPL; i++) {
+                    const int r = i * 64 + lane;
+                    if (r < R) put(r, P[1 + from * R + r]);
                 }
-            });
+            } else {
+                for (int i0 = 0; i0 < wt.rounds; i0 += 4) {
+                    double v[4];   // read before the first is written
+#pragma unroll
+                    for (int i = 0; i < 4; i++) v[i] = P[1 + from * R + min((i0 + i) * 64 + lane, R - 1)];
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+                        if ((i0 + i) * 64 + lane < R) put((i0 + i) * 64 + lane, v[i]);
+                }
+            }
             sync();
         };
-        all(rates);
         sync();
         const double w0 = produce();
         const double wk = lane < K ? w0 : 0.0;
@@ -386,16 +426,42 @@ struct WaveSys {
             uint32_t e[4], f[4];   // the next four contributions are fetched while these are added
 #pragma unroll
             for (int j = 0; j < 4; j++) e[j] = con[j * 64];
+            auto add = [&](uint32_t k, double v) __attribute__((always_inline)) { s += (int)k < 0 ? -v : v; };
+            if constexpr (QLDS) {
 #pragma clang loop unroll(disable)
-            for (int j0 = 4; j0 <= c.y; j0 += 4) {
-                const int jn = j0 < c.y ? j0 : 0;
+                for (int j0 = 4; j0 <= c.y; j0 += 4) {
+                    const int jn = j0 < c.y ? j0 : 0;
 #pragma unroll
-                for (int j = 0; j < 4; j++) f[j] = con[(jn + j) * 64];
+                    for (int j = 0; j < 4; j++) f[j] = con[(jn + j) * 64];
 #pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    const double v = at_off(e[j] & 0x7fffffffu);
-                    s += (int)e[j] < 0 ? -v : v;
-                    e[j] = f[j];
+                    for (int j = 0; j < 4; j++) {
+                        add(e[j], at_off(e[j] & 0x7fffffffu));
+                        e[j] = f[j];
+                    }
+                }
+            } else {
+                // and their values too, from global memory
+                double v[4], u[4];
+                const int j4 = c.y > 4 ? 4 : 0;
+#pragma unroll
+                for (int j = 0; j < 4; j++) f[j] = con[(j4 + j) * 64];
+#pragma unroll
+                for (int j = 0; j < 4; j++) v[j] = at_off(e[j] & 0x7fffffffu);
+#pragma clang loop unroll(disable)
+                for (int j0 = 4; j0 <= c.y; j0 += 4) {
+                    const int jn = j0 + 4 < c.y ? j0 + 4 : 0;
+                    uint32_t g[4];
+#pragma unroll
+                    for (int j = 0; j < 4; j++) g[j] = con[(jn + j) * 64];
+#pragma unroll
+                    for (int j = 0; j < 4; j++) u[j] = at_off(f[j] & 0x7fffffffu);
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        add(e[j], v[j]);
+                        e[j] = f[j];
+                        f[j] = g[j];
+                        v[j] = u[j];
+                    }
                 }
             }
             const bool pad = rc == 0xFFFFu;

@@ -1,6 +1,6 @@
 """The wave-per-cell integrator with its reaction scratch in global memory
-(more than 256 reactions, and a scratch beyond 48 KB: from 1,024 elementary
-reactions, from 878 where some are pressure dependent), against the oracle."""
+(from 878 elementary reactions, from 769 where some are pressure dependent),
+against the oracle."""
 import numpy as np
 import pytest
 
@@ -10,13 +10,13 @@ from test_gpu_wave_shapes import _opts, torch  # noqa: F401
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("K,R,pdep", [(40, 1024, False), (45, 1030, False), (36, 878, True), (41, 890, True),
-                                      (40, 1023, True), (63, 1100, True)])
+@pytest.mark.parametrize("K,R,pdep", [(40, 878, False), (45, 1030, False), (60, 900, False), (36, 769, True),
+                                      (41, 890, True), (40, 1023, True), (63, 1100, True)])
 def test_global_scratch_matches_oracle(torch, tmp_path, oracle_lib, K, R, pdep):  # noqa: F811
     from chemgen.fields import cells4096
     from chemgen.mechanism import make_mechanism, make_real_like_mechanism
     from paper_2312_13513_amd import chem
-    assert R >= (878 if pdep else 1024)   # the limits that test_wave_scratch.py holds the library to
+    assert R >= (769 if pdep else 878)   # the limits that test_wave_scratch.py holds the library to
     m = make_real_like_mechanism(seed=70 + K, K=K, R=R, E=4, n_third=30, n_lind=9, n_troe=12, n_dup=6,
                                  n_irrev=5) if pdep else make_mechanism(seed=70 + K, K=K, R=R, E=4)
     p = tmp_path / "m.mech"

@@ -60,6 +60,6 @@ def test_scratch_is_held_where_a_launch_uses_it(rows):
 def test_limits_of_the_wave_kernel(rows):
     """The reaction counts from which the wave kernel's scratch is in global
     memory; the GPU tests of that kernel rely on them."""
-    for pdep, first in ((0, 1024), (1, 878)):
+    for pdep, first in ((0, 878), (1, 769)):
         r = rows[(rows[:, 0] > 15) & (rows[:, 2] == pdep)]
         assert (r[:, 3] == (r[:, 1] >= first)).all()
