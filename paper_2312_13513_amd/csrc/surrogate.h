@@ -148,7 +148,7 @@ hipError_t launch_loss_grad(const float *out, const float *Yb, int rows, int K, 
                             bf16_t *dOut, double *loss_acc, hipStream_t s);
 // db[n] = sum over rows of d[r][n]; part: 64 x N floats of workspace.
 hipError_t launch_bias_grad(const bf16_t *d, int rows, int N, int ld, float *part, float *db, hipStream_t s);
-// Adam on FP32 master weights, BF16 copies refreshed from them.
+// Adam on FP32 master weights (launch_train_update).
 struct AdamArgs {
     float *p, *m, *v;
     const float *g;
@@ -157,6 +157,5 @@ struct AdamArgs {
     // carry the cancellation error of 0.999f (1.3e-5 relative) into v
     float lr, beta1, beta2, omb1, omb2, eps, bc1, bc2;
 };
-hipError_t launch_adam(const AdamArgs &a, hipStream_t s);
 
 }  // namespace chem

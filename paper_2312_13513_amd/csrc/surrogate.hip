@@ -891,19 +891,6 @@ __global__ void __launch_bounds__(256) bias_grad_final_kernel(const float *__res
     db[n] = s;
 }
 
-__global__ void __launch_bounds__(256) adam_kernel(AdamArgs a)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.n) return;
-    const float g = a.g[i];
-    const float m = a.beta1 * a.m[i] + a.omb1 * g;
-    const float v = a.beta2 * a.v[i] + a.omb2 * g * g;
-    a.m[i] = m;
-    a.v[i] = v;
-    const float mh = m / a.bc1, vh = v / a.bc2;
-    a.p[i] -= a.lr * mh / (sqrtf(vh) + a.eps);
-}
-
 }  // namespace
 
 hipError_t launch_gemm_bf16(const GemmArgs &g, hipStream_t s)
@@ -1136,13 +1123,6 @@ hipError_t launch_bias_grad(const bf16_t *d, int rows, int N, int ld, float *par
     hipLaunchKernelGGL(bias_grad_part_kernel, dim3(blocks_for(N, 64), kBiasChunks), dim3(64), 0, s, d, rows, N, ld,
                        part);
     hipLaunchKernelGGL(bias_grad_final_kernel, dim3(blocks_for(N, 256)), dim3(256), 0, s, part, N, db);
-    return hipGetLastError();
-}
-
-hipError_t launch_adam(const AdamArgs &a, hipStream_t s)
-{
-    if (a.n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(adam_kernel, dim3(blocks_for(a.n, 256)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -476,11 +476,16 @@ int download_logical(chem_surr_s *s, const float *dev, float *host, int64_t coun
     return CHEM_OK;
 }
 
-// The BF16 weights in all their orders from the parameters.
-hipError_t refresh_weights(const chem_surr_s *s, hipStream_t st)
+// The BF16 weights in all their orders from the parameters, after an Adam step
+// where one is given.
+hipError_t refresh_weights(const chem_surr_s *s, hipStream_t st, const chem::AdamArgs *adam = nullptr)
 {
     chem::UpdateArgs u = update_args(s);
     u.weights = 1;
+    if (adam) {
+        u.adam = 1;
+        u.o = *adam;
+    }
     return chem::launch_train_update(u, st);
 }
 
@@ -1128,11 +1133,8 @@ int chem_surrogate_adam(chem_surr s, double lr, void *stream)
     if (rc != CHEM_OK) return rc;
     if (!(lr >= 0.0) || !std::isfinite(lr)) return fail(CHEM_EINVAL, "lr must be finite and >= 0");
     s->adam_t++;
-    chem::AdamArgs a = adam_args(s, lr);
-    hipStream_t st = (hipStream_t)stream;
-    rc = check_hip(chem::launch_adam(a, st), "adam");
-    if (rc != CHEM_OK) return rc;
-    return check_hip(refresh_weights(s, st), "bf16 weights");
+    const chem::AdamArgs a = adam_args(s, lr);
+    return check_hip(refresh_weights(s, (hipStream_t)stream, &a), "adam");
 }
 
 int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, const double *Y, int64_t ldY,
@@ -1192,8 +1194,8 @@ int chem_surrogate_train_part(chem_surr s, const double *T, const double *p, con
             if (e == hipSuccess) e = backward(s, a, a.X, rr, st);
             if (e == hipSuccess) {
                 s->adam_t++;
-                e = chem::launch_adam(adam_args(s, lr), st);
-                if (e == hipSuccess) e = refresh_weights(s, st);
+                const chem::AdamArgs aa = adam_args(s, lr);
+                e = refresh_weights(s, st, &aa);
             }
         }
         if (e == hipSuccess && loss_per_epoch) {

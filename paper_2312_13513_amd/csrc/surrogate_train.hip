@@ -350,7 +350,8 @@ __global__ void __launch_bounds__(64) adam_rows_kernel(UpdateArgs a)
         load8(a.o.v + i, v);
 #pragma unroll
         for (int e = 0; e < 8; e++) {
-            // the roundings of adam_kernel
+            // these roundings whatever the surroundings: the weights of a run do not
+            // depend on the path that computed its gradients
             m[e] = fmaf(a.o.omb1, g[e], a.o.beta1 * m[e]);
             v[e] = fmaf(g[e], a.o.omb2 * g[e], a.o.beta2 * v[e]);
             const float mh = m[e] / a.o.bc1, vh = v[e] / a.o.bc2;
