@@ -1032,8 +1032,8 @@ int chem_surrogate_infer(chem_surr s, double *T, const double *p, double *Y, int
     if (rc != CHEM_OK) return rc;
     const chem::ApplyArgs aa = apply_args(s, c);
     const int sides = w.sides;
-    int64_t q = 0;
-    for (int64_t r0 = 0; r0 < n; r0 += chunk, q++) {
+    int64_t q = 0;   // passes that went to a side stream
+    for (int64_t r0 = 0; r0 < n && rc == CHEM_OK; r0 += chunk) {
         const int rr = (int)(n - r0 < chunk ? n - r0 : chunk);
         hipError_t e = chem::launch_encode(T + r0, p + r0, Y + r0, ldY, rr, K, kInPad, s->norm_dev, Xc, st);
         if (e == hipSuccess)
@@ -1043,7 +1043,10 @@ int chem_surrogate_infer(chem_surr s, double *T, const double *p, double *Y, int
             e = chem::launch_apply(aa, T + r0, p + r0, Y + r0, ldY, rr, r0, OUTc, s->nout_pad,
                                    mask ? mask + r0 : nullptr, status ? status + r0 : nullptr, fb.list + r0,
                                    pc + q, st);
-        if (e != hipSuccess) return check_hip(e, "surrogate pass");
+        if (e != hipSuccess) {
+            rc = check_hip(e, "surrogate pass");
+            break;
+        }
         hipEvent_t fork = s->fork[q % sides];
         hipStream_t sd = s->side[q % sides];
         rc = check_hip(hipEventRecord(fork, st), "fork event");
@@ -1060,11 +1063,13 @@ int chem_surrogate_infer(chem_surr s, double *T, const double *p, double *Y, int
             rc = check_hip(chem::launch_scatter_cells_ld(fb.list + r0, pc + q, rr, fb.cap, fb.T + r0, fb.Y + r0,
                                                          fb.status + r0, K, T, Y, ldY, status, sd),
                            "scatter");
-        if (rc != CHEM_OK) return rc;
+        q++;
     }
-    for (int i = 0; i < sides && rc == CHEM_OK; i++) {
-        rc = check_hip(hipEventRecord(s->joined[i], s->side[i]), "join event");
-        if (rc == CHEM_OK) rc = check_hip(hipStreamWaitEvent(st, s->joined[i], 0), "join wait");
+    // joined after an error too: what was queued reads and writes the caller's arrays
+    for (int i = 0; i < sides && i < q; i++) {
+        hipError_t e = hipEventRecord(s->joined[i], s->side[i]);
+        if (e == hipSuccess) e = hipStreamWaitEvent(st, s->joined[i], 0);
+        if (rc == CHEM_OK) rc = check_hip(e, "join");
     }
     if (rc == CHEM_OK) rc = check_hip(chem::launch_sum_i64(pc, (int)npass, count, st), "fallback count");
     return rc;

@@ -90,3 +90,42 @@ def test_captured_passes(torch, mech_dir, sized_by):  # noqa: F811
     surr.close()
     one.close()
     mech.close()
+
+
+def test_refused_call_joins_its_side_streams(torch, mech_dir):  # noqa: F811
+    """A call that the integrator refuses (a negative tolerance) after work went to
+    a side stream: the side stream is joined, so the capture it stood in can be
+    ended, and the handle serves the next call."""
+    from chemgen.fields import cells4096
+    from chemgen.mechanism import read_mechanism
+    from oracle import surrogate as S
+    from paper_2312_13513_amd import chem
+    mpy = read_mechanism(str(mech_dir / "M9.mech"))
+    f = cells4096(mpy, n=PASS + 100, seed=9)
+    mech = chem.Mechanism(str(mech_dir / "M9.mech"), 0)
+    raw = S.features(f.T, f.p, f.Y)
+    norm = np.concatenate([raw.mean(0), raw.std(0), np.zeros(mpy.K), np.full(mpy.K, 1e-9), [f.dt]])
+    surr = _surrogate(chem, mech, mpy.K, norm)
+    surr.set_pass_rows(PASS)
+    p = _dev(torch, f.p)
+    out = []
+    for _ in range(2):
+        T, Y = _dev(torch, f.T), _dev(torch, f.Y)
+        surr.infer(T, p, Y, f.dt)
+        torch.cuda.synchronize()
+        out.append((T, Y))
+        if len(out) == 1:
+            opts = chem.chem_default_opts()
+            opts.rtol = -1.0
+            Tc, Yc = _dev(torch, f.T), _dev(torch, f.Y)
+            s = torch.cuda.Stream()
+            s.wait_stream(torch.cuda.current_stream())
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.stream(s), pytest.raises(chem.ChemError, match="rtol"):
+                with torch.cuda.graph(g, stream=s):
+                    surr.infer(Tc, p, Yc, f.dt, opts=opts, stream=s)
+            torch.cuda.synchronize()
+            del g
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    surr.close()
+    mech.close()
