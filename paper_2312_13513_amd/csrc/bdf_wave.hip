@@ -1057,9 +1057,12 @@ __device__ void run_cells(Sys &S, StepLds &C, const CellIO &io, double t_end, un
     }
 }
 
-// One 64-lane wave per cell.  Two waves per SIMD: with 256 registers each
-// row of the inverse, the Nordsieck column and the rates in flight stay in
-// registers, and the second wave covers part of the first one's latencies.
+// One 64-lane wave per cell.  Two waves per SIMD: with 256 registers the row of
+// the inverse, the Nordsieck column and the rates in flight mostly stay in
+// registers, and the second wave covers part of the first one's latencies.  What
+// the compiler spills to private memory: nothing in 24 rows and, but for 60 B in 64
+// rows, in FP32; in FP64 44 to 100 B per lane in 36 rows and 90 to 200 B in 48; the
+// 64-row FP64 builds take more than 256 registers, one wave per SIMD.
 template <int NP, typename LT, int RPL, bool QLDS>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
 bdf_wave_kernel(DevMechView m, Wave64Tables wt, double *__restrict__ T, const double *__restrict__ p,

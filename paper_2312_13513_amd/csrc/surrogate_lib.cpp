@@ -94,7 +94,7 @@ struct chem_surr_s {
     // (default priority) while the later passes run.  A pass's integration
     // lasts as long as its stiffest cell, often longer than a pass, on a few
     // compute units, so the passes take kSides streams in turn and their
-    // integrations overlap (42 of 4.2 M cells, two passes: 24.8 -> 20.7 ms for
+    // integrations overlap (42 of 4.2 M cells, two passes: 24.8 -> 17.5 ms for
     // the step).  One stream when the mechanism's integrator keeps reaction
     // scratch in global memory: its few partitions rotate from call to call,
     // which keeps calls apart on one stream, not on several that take turns.

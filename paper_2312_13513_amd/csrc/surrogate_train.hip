@@ -16,9 +16,9 @@
 //    three orders the other kernels read.
 // Every product runs the layered GEMMs' MFMA sequence (16x16x32, the
 // contraction in increasing steps): the trained weights have their bits.
-// Measured (37-512-256-128-35, batch 4,096): 780 -> 57 us per minibatch (rows 26,
-// gradients 18, update 6; the rows kernel waits on weight fragments from L2 and
-// on erf and exp of its GELU derivatives).
+// Measured (37-512-256-128-35, batch 4,096): 780 -> 57 us per minibatch (rows 28,
+// gradients 18, update 6.5, the rest between launches; the rows kernel waits on
+// weight fragments from L2 and on erf and exp of its GELU derivatives).
 
 #include "surrogate_train.h"
 #include "surrogate_math.h"

@@ -86,8 +86,9 @@ struct Wave64Lds {
                                   // reaction reaches stay 0 from the start
 };
 
-// RPL: reactions per lane, kept in registers (0: any number, kept in the
-// scratch); QLDS: the scratch is in LDS.
+// RPL: reactions per lane, unrolled, whose rate constants a refresh keeps in
+// registers (0: any number, their rate constants in the scratch); QLDS: the scratch
+// is in LDS.
 template <int NP, typename LT, int RPL, bool QLDS>
 struct WaveSys {
     static constexpr int G = 64;
